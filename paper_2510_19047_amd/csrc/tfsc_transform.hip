@@ -2,15 +2,10 @@
 // tranche is Tukey-windowed and Fourier transformed once; per-tranche PSD;
 // tranches overlapping gaps are excluded).
 //
-// One block handles TB consecutive tranches of one channel: each pair of
-// tranches is windowed into LDS as the real and imaginary parts of one complex
-// sequence, transformed by a radix-2 Stockham FFT (natural order in and out,
-// twiddles from a per-block LDS table), split into the two tranches' spectra,
-// whitened, and parked in an
-// LDS tile [K][TB]; the tile is then written so that the TB tranches of a
-// frequency layer are contiguous (LAYER_MAJOR, or LAYER_MAJOR_CI with the channels of a
-// pixel adjacent) or the K bins of a tranche are contiguous (TRANCHE_MAJOR).  16-bit stores go through an FP32 staging
-// buffer and a second pass that applies a per-layer scale.
+// Consecutive tranches of a channel go in pairs as the real and imaginary parts of one complex
+// sequence through a radix-2 Stockham FFT (natural order in and out, twiddles from a per-block LDS
+// table), are split into the two tranches' spectra, whitened and stored in the layout asked for.
+// 16-bit stores go through an FP32 staging buffer and a second pass that applies a per-layer scale.
 #include "tfsc_device.hpp"
 #include "tfsc_kernels.hpp"
 
@@ -18,12 +13,11 @@ namespace tfsc {
 
 __device__ __forceinline__ bool psd_ok(double S) { return S > 0.0 && S < __builtin_huge_val(); }
 
+// Window value n of the Tukey window with tapers of `width` + 1 samples (width = floor(alpha (M - 1) / 2), -1: none).
 template <class R>
-__device__ __forceinline__ R tukey_w(int n, int M, double alpha) {
-    if (alpha <= 0.0) return (R)1;
-    int nn = min(n, M - 1 - n);
-    double width = floor(alpha * (M - 1) / 2.0);
-    if ((double)nn > width) return (R)1;
+__device__ __forceinline__ R tukey_w(int n, int M, double alpha, int width) {
+    const int nn = min(n, M - 1 - n);
+    if (nn > width) return (R)1;
     return (R)(0.5 * (1.0 + cospi(-1.0 + 2.0 * nn / (alpha * (M - 1)))));
 }
 
@@ -42,102 +36,318 @@ __device__ __forceinline__ cx<float> twiddle<float>(double frac) {
     return {c, s};
 }
 
-template <class R, class XT, class OutT, int TB>
-__global__ __launch_bounds__(256) void k_transform(TransformLaunch L, double w2) {
-    extern __shared__ unsigned char smem_raw[];
-    const int M = L.M, K = M / 2 + 1, Nt = L.Nt;
-    cx<R> *bufA = reinterpret_cast<cx<R> *>(smem_raw);
-    cx<R> *bufB = bufA + M;
-    cx<R> *tw = bufB + M;                       // M/2 twiddles exp(-2 pi i k / M)
-    cx<R> *tile = tw + M / 2;                   // [K][TB]
-    R *win = reinterpret_cast<R *>(tile + (size_t)K * TB);
+// Windowed FFT and whitening.  A thread holds 8 of the M points of a pair's complex sequence (points t + i M/8) and
+// runs three radix-2 Stockham stages on them in registers between two exchanges through LDS, so an M-point transform
+// makes ceil(log2(M) / 3) exchanges instead of log2(M); M/8 threads share a transform and a block of 256 (512 for
+// M = 4096) runs 2048 / M of them side by side on consecutive tranches.  The butterflies, their twiddles and their
+// order are those of the plain radix-2 algorithm, so the results are the same bits.
+//
+// The first stages take their points from the series itself; the last exchange puts Z in natural order for the split
+// of the two tranches.  A thread keeps the whitened values of NIT transforms (a pair of tranches of each of the CC
+// channels of a cell, or two pairs of one channel) and writes a run of at least 32 bytes per frequency layer, NF times
+// per block.  Consecutive tiles go to one XCD, whose L2 joins the runs of neighbouring tiles (113.7 MB written for a
+// 100.8 MB store).
+//
+// Bound: latency, at three waves per SIMD (the registers and 53 KB of LDS allow no more); the vector ALU is busy for
+// half the time, the LDS for a third.  Two years of A+E, FP32 (100.7 MB in, 100.8 MB out): 97 us, 2.1 TB/s, against
+// 520 us with one exchange per stage, a branch (and a wait) around every load and 8-byte stores.  Holding the runs of
+// four tranches, the window or the whitening factors in registers across the transforms spilled and took 139-168 us.
+// -i w: the twiddle a quarter turn on.  For a twiddle below exp(-i pi / 4) it has the table's bits; from there on the
+// table's own entry is read (its sine and cosine of pi / 4 differ in the last place).
+template <class R>
+__device__ __forceinline__ cx<R> mul_neg_i(cx<R> w) { return {w.im, -w.re}; }
 
-    const int c = blockIdx.y;
-    const int m0 = blockIdx.x * TB;
-    for (int k = threadIdx.x; k < M / 2; k += blockDim.x) tw[k] = twiddle<R>((double)k / M);
-    for (int n = threadIdx.x; n < M; n += blockDim.x) win[n] = tukey_w<R>(n, M, L.alpha);
-    const XT *x = reinterpret_cast<const XT *>(L.x) + (size_t)c * M * Nt;
-    __syncthreads();
-
-    // Two real tranches per complex FFT: z = x_m + i x_{m+1}, whose transform Z gives
-    // X_m[k] = (Z[k] + conj Z[M-k]) / 2 and X_{m+1}[k] = (Z[k] - conj Z[M-k]) / (2i).
-    static_assert(TB % 2 == 0, "tranches are transformed in pairs");
-    for (int tt = 0; tt < TB; tt += 2) {
-        const int m = m0 + tt;
-        if (m >= Nt) break;  // uniform across the block
-        const bool two = m + 1 < Nt;
-        for (int n = threadIdx.x; n < M; n += blockDim.x)
-            bufA[n] = {(R)x[(size_t)m * M + n] * win[n], two ? (R)x[(size_t)(m + 1) * M + n] * win[n] : (R)0};
-        __syncthreads();
-        cx<R> *src = bufA, *dst = bufB;
-        for (int Ns = 1; Ns < M; Ns <<= 1) {
-            for (int j = threadIdx.x; j < M / 2; j += blockDim.x) {
-                const int kk = j & (Ns - 1);
-                cx<R> a = src[j], b = src[j + M / 2];
-                cx<R> w = tw[kk * (M / (2 * Ns))];
-                b = cmul(b, w);
-                const int d = ((j - kk) << 1) + kk;
-                dst[d] = cadd(a, b);
-                dst[d + Ns] = csub(a, b);
-            }
-            __syncthreads();
-            cx<R> *t = src;
-            src = dst;
-            dst = t;
-        }
-        for (int k = threadIdx.x; k < K; k += blockDim.x) {
-            const cx<R> zk = src[k], zn = src[(M - k) & (M - 1)];
-            const cx<R> X[2] = {{(R)0.5 * (zk.re + zn.re), (R)0.5 * (zk.im - zn.im)},
-                                {(R)0.5 * (zk.im + zn.im), (R)0.5 * (zn.re - zk.re)}};
-            for (int j = 0; j < (two ? 2 : 1); ++j) {
-                const int mj = m + j;
-                const double S = L.psd_tf ? L.psd_tf[(size_t)k * Nt + mj] : L.psd0[k] * L.mu[mj];
-                // a bin whose PSD is not positive and finite (DC or Nyquist may carry 0 or inf)
-                // gets pixel 0 rather than inf or NaN; its template weight is 0 as well
-                const double sc = L.keep[mj] != 0 && psd_ok(S) ? sqrt(2.0 * L.dt / ((double)M * w2 * S)) : 0.0;
-                tile[(size_t)k * TB + tt + j] = cscale(X[j], (R)sc);
-            }
-        }
-        __syncthreads();
-    }
-    // write out the tile
-    const int ntb = min(TB, Nt - m0);
-    if (L.out_layout == 0 || L.out_layout == 2) {
-        for (int e = threadIdx.x; e < K * TB; e += blockDim.x) {
-            const int k = e / TB, tt = e % TB;
-            if (tt >= ntb) continue;
-            cx<R> v = tile[e];
-            size_t idx = L.out_layout == 0 ? ((size_t)c * K + k) * Nt + (m0 + tt)
-                                           : ((size_t)k * Nt + (m0 + tt)) * L.C + c;
-            reinterpret_cast<OutT *>(L.pix)[2 * idx] = (OutT)v.re;
-            reinterpret_cast<OutT *>(L.pix)[2 * idx + 1] = (OutT)v.im;
-        }
-    } else {
-        for (int e = threadIdx.x; e < K * TB; e += blockDim.x) {
-            const int tt = e / K, k = e % K;
-            if (tt >= ntb) continue;
-            cx<R> v = tile[(size_t)k * TB + tt];
-            size_t idx = ((size_t)c * Nt + (m0 + tt)) * K + k;
-            reinterpret_cast<OutT *>(L.pix)[2 * idx] = (OutT)v.re;
-            reinterpret_cast<OutT *>(L.pix)[2 * idx + 1] = (OutT)v.im;
-        }
-    }
+// (a, b) -> (a + w b, a - w b).  The product's roundings are written out (b.im w.im and b.re w.im are rounded, the rest is
+// fused): left to the compiler they would depend on whether w comes from the table or from mul_neg_i.
+template <class R>
+__device__ __forceinline__ void butterfly(cx<R> &a, cx<R> &b, cx<R> w) {
+    const R p = b.im * w.im, q = b.re * w.im;
+    const cx<R> bw = {fma(b.re, w.re, -p), fma(b.im, w.re, q)};
+    b = csub(a, bw);
+    a = cadd(a, bw);
 }
 
-// per-layer maximum |component| of an FP32 LAYER_MAJOR staging store
-__global__ void k_layer_absmax(int C, int K, int Nt, const float *__restrict__ st, uint32_t *__restrict__ mx) {
-    const int layer = blockIdx.x;  // c * K + k
-    float v = 0.0f;
-    const float *row = st + (size_t)layer * Nt * 2;
-    for (int e = threadIdx.x; e < 2 * Nt; e += blockDim.x) v = fmaxf(v, fabsf(row[e]));
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    __shared__ float sh[16];
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float m = 0.0f;
-        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) m = fmaxf(m, sh[w]);
-        mx[layer] = __float_as_uint(m);
+// A complex value in LDS, moved with one 16-byte (FP64) or 8-byte (FP32) access.
+template <class R>
+struct alignas(2 * sizeof(R)) lds_cx {
+    R re, im;
+    __device__ __forceinline__ operator cx<R>() const { return {re, im}; }
+};
+
+// Padding: one element in 8 (the stage outputs lie 8 apart), one in 16 for the twiddles.  The lanes' positions are
+// base + constant, so that every offset is an immediate of the access.
+__host__ __device__ constexpr int lds_pos(int i) { return i + (i >> 3); }
+__host__ __device__ constexpr int tw_pos(int i) { return i + (i >> 6); }
+
+// Three radix-2 stages on the thread's points v[i] = src[t + i M/8], at sub-transform length NS, kk = t mod NS.
+template <int M, int NS, class R>
+__device__ __forceinline__ void stages3(cx<R> (&v)[8], const lds_cx<R> *tw, int kk) {
+    const cx<R> w1 = tw[tw_pos(kk * (M / (2 * NS)))];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) butterfly(v[i], v[i + 4], w1);  // v[i] = (i, b0 = 0), v[i + 4] = (i, b0 = 1)
+    const cx<R> w2 = tw[tw_pos(kk * (M / (4 * NS)))], w2i = tw[tw_pos((kk + NS) * (M / (4 * NS)))];
+    butterfly(v[0], v[2], w2);
+    butterfly(v[1], v[3], w2);
+    butterfly(v[4], v[6], w2i);
+    butterfly(v[5], v[7], w2i);
+    constexpr int Q = M / (8 * NS);
+    const cx<R> w3 = tw[tw_pos(kk * Q)], w3b = tw[tw_pos((kk + NS) * Q)], w3d = tw[tw_pos((kk + 3 * NS) * Q)];
+    butterfly(v[0], v[1], w3);             // b0 = 0, b1 = 0: outputs 0 and 4
+    butterfly(v[4], v[5], w3b);            // b0 = 1, b1 = 0: outputs 1 and 5
+    butterfly(v[2], v[3], mul_neg_i(w3));  // b0 = 0, b1 = 1: outputs 2 and 6
+    butterfly(v[6], v[7], w3d);            // b0 = 1, b1 = 1: outputs 3 and 7
+}
+
+// Output q of stages3 belongs at 8 (t - kk) + kk + q NS.
+template <int NS, class R>
+__device__ __forceinline__ void store8(const cx<R> (&v)[8], lds_cx<R> *buf, int t, int kk) {
+    constexpr int from[8] = {0, 4, 2, 6, 1, 5, 3, 7};
+    lds_cx<R> *p = buf + lds_pos(8 * (t - kk) + kk);
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+        p[NS == 1 ? q : lds_pos(q * NS)] = {v[from[q]].re, v[from[q]].im};
+}
+
+template <int T8, class R>
+__device__ __forceinline__ void load8(cx<R> (&v)[8], const lds_cx<R> *buf, int t) {
+    const lds_cx<R> *p = buf + lds_pos(t);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = p[lds_pos(i * T8)];
+}
+
+// One block's transforms: CC channels (1, or all of a channel-interleaved cell) of TB tranches per group of M/8
+// threads.  Tranches are transformed in pairs, z = x_m + i x_{m+1}: X_m[k] = (Z[k] + conj Z[M-k]) / 2 and
+// X_{m+1}[k] = (Z[k] - conj Z[M-k]) / (2i).
+template <class R, class XT, class OutT, int M, int CC, int NIT, int NF>
+__global__ __launch_bounds__(M == 4096 ? 512 : 256, CC == 3 ? 2 : 3) void k_transform(
+    TransformLaunch L, double w2, int width, uint32_t *__restrict__ layer_max, int n_tiles) {
+    constexpr int TB = 2 * NIT / CC;  // tranches per group
+    constexpr int K = M / 2 + 1, T8 = M / 8, NT = M == 4096 ? 512 : 256, NG = NT / T8;
+    __shared__ lds_cx<R> tw[tw_pos(M / 2)];        // exp(-2 pi i k / M)
+    __shared__ lds_cx<R> bufs[NG * lds_pos(M)];
+    const int Nt = L.Nt;
+    const int t0 = threadIdx.x & (T8 - 1), grp = threadIdx.x / T8;
+    lds_cx<R> *buf = bufs + grp * lds_pos(M);
+    for (int k = threadIdx.x; k < M / 2; k += NT) {
+        const cx<R> w = twiddle<R>((double)k / M);
+        tw[tw_pos(k)] = {w.re, w.im};
+    }
+    // tiles of consecutive tranches on one XCD (workgroups go round the 8 XCDs)
+    const int per_xcd = (n_tiles + 7) / 8;
+    const int tile = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per_xcd || tile >= n_tiles) return;
+    const int c0 = blockIdx.y * CC;
+    // whitening factor for the PSD value S of a tranche with its keep mark; a bin whose PSD is not positive and finite
+    // (DC or Nyquist may carry 0 or inf) gets pixel 0 rather than inf or NaN; its template weight is 0 as well.  No
+    // branches here nor in the loads: the latencies of a thread's values then overlap.
+    auto scale = [&](double S, bool kept) -> R {
+        const bool ok = kept && psd_ok(S);
+        const double v = sqrt(2.0 * L.dt / ((double)M * w2 * (ok ? S : 1.0)));
+        return (R)(ok ? v : 0.0);
+    };
+    auto psd = [&](int k, int mj, double mu) -> double {  // mj < Nt
+        return L.psd_tf ? L.psd_tf[(size_t)k * Nt + mj] : L.psd0[k] * mu;
+    };
+#pragma unroll 1
+    for (int fl = 0; fl < NF; ++fl) {
+        const int m0 = ((tile * NF + fl) * NG + grp) * TB;
+        // held[it][i][tr]: bin k = t + i M/8 of tranche m + tr; DC and Nyquist are real, so bin 0 holds (DC, Nyquist)
+        cx<OutT> held[NIT][4][2] = {};
+#pragma unroll 1
+        for (int it = 0; it < NIT; ++it) {
+            const int c = c0 + it % CC, m = m0 + 2 * (it / CC);
+            // the thread's index anew for each transform: the addresses, window and PSD values that depend on it are then
+            // formed where they are used instead of being held in registers (and spilled) across the transforms
+            int t = t0;
+            asm volatile("" : "+v"(t));
+            cx<R> v[8];
+            {
+                // tranches past the end read the last one and count as zero
+                const int ma = min(m, Nt - 1), mb = min(m + 1, Nt - 1);
+                const XT *xa = reinterpret_cast<const XT *>(L.x) + ((size_t)c * Nt + ma) * M + t;
+                const XT *xb = reinterpret_cast<const XT *>(L.x) + ((size_t)c * Nt + mb) * M + t;
+                XT a[8], b[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    a[i] = xa[i * T8];
+                    b[i] = xb[i * T8];
+                }
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const R win = tukey_w<R>(t + i * T8, M, L.alpha, width);
+                    v[i].re = m < Nt ? (R)a[i] * win : (R)0;
+                    v[i].im = m + 1 < Nt ? (R)b[i] * win : (R)0;
+                }
+            }
+            __syncthreads();  // the twiddles are there, and the last transform's split has read its points
+            stages3<M, 1>(v, tw, 0);
+            store8<1>(v, buf, t, 0);
+            __syncthreads();
+            load8<T8>(v, buf, t);
+            stages3<M, 8>(v, tw, t & 7);
+            __syncthreads();
+            store8<8>(v, buf, t, t & 7);
+            __syncthreads();
+            if constexpr (M >= 512) {
+                load8<T8>(v, buf, t);
+                stages3<M, 64>(v, tw, t & 63);
+                __syncthreads();
+                store8<64>(v, buf, t, t & 63);
+                __syncthreads();
+            }
+            if constexpr (M >= 4096) {
+                load8<T8>(v, buf, t);
+                stages3<M, 512>(v, tw, t & 511);
+                __syncthreads();
+                store8<512>(v, buf, t, t & 511);
+                __syncthreads();
+            }
+            constexpr int LEFT = M >= 512 ? (M >= 4096 ? M / 4096 : M / 512) : M / 64;  // stages left: 1, 2 or 4 points
+            if constexpr (LEFT == 2) {
+                constexpr int NS = M / 2;
+                load8<T8>(v, buf, t);
+                __syncthreads();
+                lds_cx<R> *p = buf + lds_pos(t);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    butterfly(v[i], v[i + 4], (cx<R>)tw[tw_pos(t + i * T8)]);
+                    p[lds_pos(i * T8)] = {v[i].re, v[i].im};
+                    p[lds_pos(i * T8 + NS)] = {v[i + 4].re, v[i + 4].im};
+                }
+                __syncthreads();
+            } else if constexpr (LEFT == 4) {
+                constexpr int NS = M / 4;
+                load8<T8>(v, buf, t);
+                __syncthreads();
+                lds_cx<R> *p = buf + lds_pos(t);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const int kk = t + i * T8;  // < NS
+                    const cx<R> wa = tw[tw_pos(2 * kk)], wb = tw[tw_pos(kk)], wbi = tw[tw_pos(kk + NS)];
+                    butterfly(v[i], v[i + 4], wa);
+                    butterfly(v[i + 2], v[i + 6], wa);
+                    butterfly(v[i], v[i + 2], wb);        // b0 = 0: outputs 0 and 2
+                    butterfly(v[i + 4], v[i + 6], wbi);   // b0 = 1: outputs 1 and 3
+                    p[lds_pos(i * T8)] = {v[i].re, v[i].im};
+                    p[lds_pos(i * T8 + NS)] = {v[i + 4].re, v[i + 4].im};
+                    p[lds_pos(i * T8 + 2 * NS)] = {v[i + 2].re, v[i + 2].im};
+                    p[lds_pos(i * T8 + 3 * NS)] = {v[i + 6].re, v[i + 6].im};
+                }
+                __syncthreads();
+            }
+            // the whitening factors, where the transform's registers are free (held over a cell's channels they would spill)
+            const int ma = min(m, Nt - 1), mb = min(m + 1, Nt - 1);
+            const double mua = L.psd_tf ? 1.0 : L.mu[ma], mub = L.psd_tf ? 1.0 : L.mu[mb];
+            const bool ka = L.keep[ma] != 0, kb = L.keep[mb] != 0;
+            R sc[4][2], scn[2] = {};
+            {
+                double sa[4], sb[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    sa[i] = psd(t + i * T8, ma, mua);
+                    sb[i] = psd(t + i * T8, mb, mub);
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    sc[i][0] = scale(sa[i], ka);
+                    sc[i][1] = scale(sb[i], kb);
+                }
+                if (t == 0) {
+                    scn[0] = scale(psd(M / 2, ma, mua), ka);
+                    scn[1] = scale(psd(M / 2, mb, mub), kb);
+                }
+            }
+            // the oldest transform's values stand first after the last turn
+#pragma unroll
+            for (int q = 0; q + 1 < NIT; ++q)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    held[q][i][0] = held[q + 1][i][0];
+                    held[q][i][1] = held[q + 1][i][1];
+                }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int k = t + i * T8;
+                const cx<R> zk = buf[lds_pos(t) + lds_pos(i * T8)], zn = buf[lds_pos((M - k) & (M - 1))];
+                cx<R> X[2] = {{(R)0.5 * (zk.re + zn.re), (R)0.5 * (zk.im - zn.im)},
+                              {(R)0.5 * (zk.im + zn.im), (R)0.5 * (zn.re - zk.re)}};
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    cx<R> o = cscale(X[j], sc[i][j]);
+                    if (i == 0 && t == 0) {
+                        const cx<R> zq = buf[lds_pos(M / 2)];
+                        o.im = (j == 0 ? zq.re : zq.im) * scn[j];
+                    }
+                    held[NIT - 1][i][j] = {(OutT)o.re, (OutT)o.im};
+                }
+            }
+        }
+
+        OutT *pix = reinterpret_cast<OutT *>(L.pix);
+        auto put = [&](int k, int q, int j, cx<OutT> o) {  // the pixel of transform q, tranche j of its pair
+            const int c = c0 + q % CC, m = m0 + 2 * (q / CC) + j;
+            if (m >= Nt) return;
+            const size_t idx = L.out_layout == 0   ? ((size_t)c * K + k) * Nt + m
+                               : L.out_layout == 1 ? ((size_t)c * Nt + m) * K + k
+                                                   : ((size_t)k * Nt + m) * L.C + c;
+            reinterpret_cast<cx<OutT> *>(pix)[idx] = o;
+        };
+        // one 16-byte store per FP32 A+E cell
+        auto put_cells = [&](int k, const cx<OutT> (&a)[2], const cx<OutT> (&b)[2], int q) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int m = m0 + 2 * (q / CC) + j;
+                if (m >= Nt) continue;
+                reinterpret_cast<float4 *>(pix)[(size_t)k * Nt + m] =
+                    float4{(float)a[j].re, (float)a[j].im, (float)b[j].re, (float)b[j].im};
+            }
+        };
+        auto put_row = [&](int k, const cx<OutT> (&row)[NIT][2]) {
+            if constexpr (CC == 2 && sizeof(OutT) == 4) {
+#pragma unroll
+                for (int q = 0; q < NIT; q += 2) put_cells(k, row[q], row[q + 1], q);
+            } else {
+#pragma unroll
+                for (int q = 0; q < NIT; ++q)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) put(k, q, j, row[q][j]);
+            }
+            if constexpr (sizeof(OutT) == 4)
+                if (layer_max) {
+#pragma unroll
+                    for (int cc = 0; cc < CC; ++cc) {
+                        float mx = 0.0f;
+#pragma unroll
+                        for (int q = cc; q < NIT; q += CC)
+#pragma unroll
+                            for (int j = 0; j < 2; ++j)
+                                mx = fmaxf(fmaxf(mx, fabsf((float)row[q][j].re)), fabsf((float)row[q][j].im));
+                        atomicMax(layer_max + (size_t)(c0 + cc) * K + k, __float_as_uint(mx));
+                    }
+                }
+        };
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int k = t0 + i * T8;
+            cx<OutT> row[NIT][2];
+#pragma unroll
+            for (int q = 0; q < NIT; ++q)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) row[q][j] = held[q][i][j];
+            if (i == 0 && t0 == 0) {
+                cx<OutT> nyq[NIT][2];
+#pragma unroll
+                for (int q = 0; q < NIT; ++q)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        const cx<OutT> o = row[q][j];
+                        nyq[q][j] = {o.im, o.im - o.im};
+                        row[q][j] = {o.re, o.re - o.re};
+                    }
+                put_row(M / 2, nyq);
+            }
+            put_row(k, row);
+        }
     }
 }
 
@@ -159,27 +369,34 @@ constexpr float q_full = 1.0f;
 template <>
 constexpr float q_full<int16_t> = 32767.0f;
 
-template <class Q>
-__global__ void k_quantize(int C, int K, int Nt, int layout, const float *__restrict__ st,
-                           const uint32_t *__restrict__ mx, float *__restrict__ layer_scale, Q *__restrict__ out) {
-    const int layer = blockIdx.y;
-    const int c = layer / K, k = layer % K;
-    float m = __uint_as_float(mx[layer]);
-    float scale = m > 0.0f ? m / q_full<Q> : 1.0f;
-    float inv = m > 0.0f ? q_full<Q> / m : 1.0f;
-    if (blockIdx.x == 0 && threadIdx.x == 0) layer_scale[layer] = scale;
-    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < Nt; t += gridDim.x * blockDim.x) {
-        const float *src = st + ((size_t)layer * Nt + t) * 2;
-        size_t idx = layout == 0 ? ((size_t)layer * Nt + t)
-                                 : (layout == 1 ? (((size_t)c * Nt + t) * K + k) : (((size_t)k * Nt + t) * C + c));
-        out[2 * idx] = to_q<Q>(src[0] * inv);
-        out[2 * idx + 1] = to_q<Q>(src[1] * inv);
+// Scale and round the FP32 staging store, which has the final layout, to 16 bits: one streaming pass.  A block works
+// on one row of the layout (blockIdx.y): a layer (layout 0), a tranche of a channel (1) or the cells of a bin (2).
+template <class Q, int LAYOUT>
+__global__ __launch_bounds__(256) void k_quantize(int C, int K, int Nt, const float2 *__restrict__ st,
+                                                  const uint32_t *__restrict__ mx, float *__restrict__ layer_scale,
+                                                  Q *__restrict__ out) {
+    const int row = blockIdx.y, len = LAYOUT == 0 ? Nt : (LAYOUT == 1 ? K : Nt * C);
+    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < len; e += gridDim.x * blockDim.x) {
+        const int layer = LAYOUT == 0 ? row : (LAYOUT == 1 ? row / Nt * K + e : e % C * K + row);
+        const float m = __uint_as_float(mx[layer]);
+        const float inv = m > 0.0f ? q_full<Q> / m : 1.0f;
+        // one writer per layer: the first element of its row (its first tranche)
+        if (LAYOUT == 0 ? e == 0 : (LAYOUT == 1 ? row % Nt == 0 : e < C))
+            layer_scale[layer] = m > 0.0f ? m / q_full<Q> : 1.0f;
+        const size_t at = (size_t)row * len + e;
+        const float2 v = st[at];
+        struct alignas(4) Pair {
+            Q re, im;
+        };
+        reinterpret_cast<Pair *>(out)[at] = Pair{to_q<Q>(v.x * inv), to_q<Q>(v.y * inv)};
     }
 }
 
 __global__ void k_weights(int K, int Nt, const double *__restrict__ psd0, const double *__restrict__ mu,
-                          const uint8_t *__restrict__ keep, double *__restrict__ inv_asd, double *__restrict__ tw) {
+                          const uint8_t *__restrict__ keep, double *__restrict__ inv_asd, double *__restrict__ tw,
+                          uint32_t *__restrict__ layer_max, int n_layers) {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (layer_max && i < n_layers) layer_max[i] = 0u;
     if (i < K) inv_asd[i] = psd_ok(psd0[i]) ? 1.0 / sqrt(psd0[i]) : 0.0;
     if (i < Nt) tw[i] = keep[i] && psd_ok(mu[i]) ? 1.0 / sqrt(mu[i]) : 0.0;
 }
@@ -189,7 +406,9 @@ __global__ void k_weights(int K, int Nt, const double *__restrict__ psd0, const 
 // u_k = 1/sqrt(S0_k) and rho_mk = sqrt(S0_k / S_m(f_k)); block 0 also writes w_m = keep_m.
 __global__ __launch_bounds__(256) void k_weights_tf(int K, int Nt, const double *__restrict__ psd,
                                                    const uint8_t *__restrict__ keep, double *__restrict__ inv_asd,
-                                                   double *__restrict__ tw, float *__restrict__ rho) {
+                                                   double *__restrict__ tw, float *__restrict__ rho,
+                                                   uint32_t *__restrict__ layer_max, int C) {
+    if (layer_max && (int)threadIdx.x < C) layer_max[threadIdx.x * K + blockIdx.x] = 0u;
     __shared__ double part[256];
     const int k = blockIdx.x;
     const double *row = psd + (size_t)k * Nt;
@@ -225,71 +444,103 @@ static double window_w2(int M, double alpha) {
     return s / M;
 }
 
-template <class R, class XT, class OutT, int TB>
-static hipError_t run_fft(const TransformLaunch &L, TransformLaunch Lw, double w2, hipStream_t st) {
-    const int M = L.M, K = M / 2 + 1;
-    size_t shmem = sizeof(cx<R>) * (2 * (size_t)M + M / 2 + (size_t)K * TB) + sizeof(R) * M;
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_transform<R, XT, OutT, TB>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        attr_set = true;
+template <class R, class XT, class OutT, int M, int CC, int NIT, int NF>
+static hipError_t run_fft_m(const TransformLaunch &L, double w2, uint32_t *layer_max, hipStream_t st) {
+    const int threads = M == 4096 ? 512 : 256, n_grp = threads / (M / 8);
+    const int per_block = NF * n_grp * (2 * NIT / CC), n_tiles = (L.Nt + per_block - 1) / per_block;
+    const dim3 grid((unsigned)((n_tiles + 7) / 8 * 8), (unsigned)(L.C / CC));
+    const int width = L.alpha > 0.0 ? (int)floor(L.alpha * (M - 1) / 2.0) : -1;
+    hipLaunchKernelGGL((k_transform<R, XT, OutT, M, CC, NIT, NF>), grid, dim3(threads), 0, st, L, w2, width, layer_max, n_tiles);
+    return hipGetLastError();
+}
+
+// FP64 arithmetic up to M = 2048, FP32 for M = 4096.
+template <class R, class XT, class OutT, int CC, int NIT, int NF>
+static hipError_t run_fft_t(const TransformLaunch &L, double w2, uint32_t *layer_max, hipStream_t st) {
+    if constexpr (sizeof(R) == 4) {
+        if (L.M == 4096) return run_fft_m<R, XT, OutT, 4096, CC, NIT, NF>(L, w2, layer_max, st);
+    } else {
+        switch (L.M) {
+            case 64: return run_fft_m<R, XT, OutT, 64, CC, NIT, NF>(L, w2, layer_max, st);
+            case 128: return run_fft_m<R, XT, OutT, 128, CC, NIT, NF>(L, w2, layer_max, st);
+            case 256: return run_fft_m<R, XT, OutT, 256, CC, NIT, NF>(L, w2, layer_max, st);
+            case 512: return run_fft_m<R, XT, OutT, 512, CC, NIT, NF>(L, w2, layer_max, st);
+            case 1024: return run_fft_m<R, XT, OutT, 1024, CC, NIT, NF>(L, w2, layer_max, st);
+            case 2048: return run_fft_m<R, XT, OutT, 2048, CC, NIT, NF>(L, w2, layer_max, st);
+        }
     }
-    dim3 grid((unsigned)((L.Nt + TB - 1) / TB), (unsigned)L.C);
-    hipLaunchKernelGGL((k_transform<R, XT, OutT, TB>), grid, dim3(256), shmem, st, Lw, w2);
+    return hipErrorInvalidValue;
+}
+
+// Channel-interleaved cells take all their channels in one block, the other layouts one channel.  NIT: transforms
+// held until the store, chosen for runs of at least 64 bytes per frequency layer.  FP64 transforms (M <= 2048) run
+// 256 threads, FP32 ones (M = 4096) 512.  The 16-byte stores of FP32 A+E cells need a store aligned to them; another one
+// takes the one-channel form, which writes any layout 8 or 16 bytes at a time.
+template <class R, class XT, class OutT>
+static hipError_t run_fft(const TransformLaunch &L, double w2, uint32_t *layer_max, hipStream_t st) {
+    constexpr int D = sizeof(OutT) / 4;
+    if (L.out_layout != 2 || L.C == 1 || reinterpret_cast<uintptr_t>(L.pix) % 16 != 0)
+        return run_fft_t<R, XT, OutT, 1, 2, 2 / D>(L, w2, layer_max, st);
+    if (L.C == 2) return run_fft_t<R, XT, OutT, 2, 2, 2 / D>(L, w2, layer_max, st);
+    return run_fft_t<R, XT, OutT, 3, 3, 2 / D>(L, w2, layer_max, st);
+}
+
+template <class Q>
+static hipError_t run_quantize(const TransformLaunch &L, const uint32_t *mx, hipStream_t st) {
+    const int K = L.M / 2 + 1;
+    const int rows = L.out_layout == 0 ? L.C * K : (L.out_layout == 1 ? L.C * L.Nt : K);
+    const int len = L.out_layout == 0 ? L.Nt : (L.out_layout == 1 ? K : L.Nt * L.C);
+    const dim3 g((unsigned)((len + 255) / 256 > 8 ? 8 : (len + 255) / 256), (unsigned)rows);
+    const float2 *src = reinterpret_cast<const float2 *>(L.ws);
+    Q *out = reinterpret_cast<Q *>(L.pix);
+    if (L.out_layout == 0)
+        hipLaunchKernelGGL((k_quantize<Q, 0>), g, dim3(256), 0, st, L.C, K, L.Nt, src, mx, L.layer_scale, out);
+    else if (L.out_layout == 1)
+        hipLaunchKernelGGL((k_quantize<Q, 1>), g, dim3(256), 0, st, L.C, K, L.Nt, src, mx, L.layer_scale, out);
+    else
+        hipLaunchKernelGGL((k_quantize<Q, 2>), g, dim3(256), 0, st, L.C, K, L.Nt, src, mx, L.layer_scale, out);
     return hipGetLastError();
 }
 
 hipError_t launch_transform(const TransformLaunch &L, hipStream_t st) {
     const int K = L.M / 2 + 1;
     const double w2 = window_w2(L.M, L.alpha);
-    int nw = K > L.Nt ? K : L.Nt;
-    if (L.psd_tf)
-        hipLaunchKernelGGL(k_weights_tf, dim3(K), dim3(256), 0, st, K, L.Nt, L.psd_tf, L.keep, L.inv_asd,
-                           L.tranche_w, L.rho);
-    else
-        hipLaunchKernelGGL(k_weights, dim3((nw + 255) / 256), dim3(256), 0, st, K, L.Nt, L.psd0, L.mu, L.keep,
-                           L.inv_asd, L.tranche_w);
     const bool q16 = L.out_dtype == 2 || L.out_dtype == 3 || L.out_dtype == 4;
-    TransformLaunch Lw = L;
-    hipError_t e;
-    // The FFT runs in FP64 whenever the tile fits in LDS (M <= 2048): whitening divides by
-    // sqrt(S0), which near the TDI nulls is ~1e5 smaller than at low frequency, so FP32 FFT
-    // rounding (set by the red low-frequency power) would be amplified there.
-    const bool big = L.M > 2048;
+    uint32_t *mx = nullptr;  // 16-bit stores: the layers' largest |component|, after the staging store in the workspace
     if (q16) {
-        // FP32 LAYER_MAJOR staging, then per-layer scale and quantisation
-        Lw.pix = L.ws;
-        Lw.out_layout = 0;
-        if (L.x_dtype == 0)
-            e = big ? run_fft<float, double, float, 2>(L, Lw, w2, st) : run_fft<double, double, float, 2>(L, Lw, w2, st);
-        else
-            e = big ? run_fft<float, float, float, 2>(L, Lw, w2, st) : run_fft<double, float, float, 2>(L, Lw, w2, st);
-        if (e != hipSuccess) return e;
         size_t st_bytes = sizeof(float) * 2 * (size_t)L.C * K * L.Nt;
         st_bytes = (st_bytes + 255) / 256 * 256;
-        uint32_t *mx = reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(L.ws) + st_bytes);
-        hipLaunchKernelGGL(k_layer_absmax, dim3(L.C * K), dim3(256), 0, st, L.C, K, L.Nt,
-                           reinterpret_cast<const float *>(L.ws), mx);
-        dim3 g((unsigned)((L.Nt + 255) / 256 > 8 ? 8 : (L.Nt + 255) / 256), (unsigned)(L.C * K));
-        if (L.out_dtype == 4)
-            hipLaunchKernelGGL(k_quantize<int16_t>, g, dim3(256), 0, st, L.C, K, L.Nt, L.out_layout,
-                               reinterpret_cast<const float *>(L.ws), mx, L.layer_scale,
-                               reinterpret_cast<int16_t *>(L.pix));
-        else if (L.out_dtype == 3)
-            hipLaunchKernelGGL(k_quantize<__half>, g, dim3(256), 0, st, L.C, K, L.Nt, L.out_layout,
-                               reinterpret_cast<const float *>(L.ws), mx, L.layer_scale,
-                               reinterpret_cast<__half *>(L.pix));
-        else
-            hipLaunchKernelGGL(k_quantize<__hip_bfloat16>, g, dim3(256), 0, st, L.C, K, L.Nt, L.out_layout,
-                               reinterpret_cast<const float *>(L.ws), mx, L.layer_scale,
-                               reinterpret_cast<__hip_bfloat16 *>(L.pix));
-        return hipGetLastError();
+        mx = reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(L.ws) + st_bytes);
     }
-    if (L.out_dtype == 0) return big ? hipErrorInvalidValue : run_fft<double, double, double, 2>(L, Lw, w2, st);
+    int nw = K > L.Nt ? K : L.Nt;
+    if (q16 && L.C * K > nw) nw = L.C * K;
+    if (L.psd_tf)
+        hipLaunchKernelGGL(k_weights_tf, dim3(K), dim3(256), 0, st, K, L.Nt, L.psd_tf, L.keep, L.inv_asd,
+                           L.tranche_w, L.rho, mx, L.C);
+    else
+        hipLaunchKernelGGL(k_weights, dim3((nw + 255) / 256), dim3(256), 0, st, K, L.Nt, L.psd0, L.mu, L.keep,
+                           L.inv_asd, L.tranche_w, mx, L.C * K);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    // The FFT runs in FP64 for M <= 2048: whitening divides by sqrt(S0), which near the TDI nulls is ~1e5 smaller
+    // than at low frequency, so FP32 FFT rounding (set by the red low-frequency power) would be amplified there.
+    const bool big = L.M > 2048;
+    if (q16) {
+        // FP32 staging in the store's layout with the layers' maxima, then per-layer scale and quantisation
+        TransformLaunch Lw = L;
+        Lw.pix = L.ws;
+        if (L.x_dtype == 0)
+            e = big ? run_fft<float, double, float>(Lw, w2, mx, st) : run_fft<double, double, float>(Lw, w2, mx, st);
+        else
+            e = big ? run_fft<float, float, float>(Lw, w2, mx, st) : run_fft<double, float, float>(Lw, w2, mx, st);
+        if (e != hipSuccess) return e;
+        if (L.out_dtype == 4) return run_quantize<int16_t>(L, mx, st);
+        return L.out_dtype == 3 ? run_quantize<__half>(L, mx, st) : run_quantize<__hip_bfloat16>(L, mx, st);
+    }
+    if (L.out_dtype == 0) return big ? hipErrorInvalidValue : run_fft<double, double, double>(L, w2, nullptr, st);
     if (L.x_dtype == 0)
-        return big ? run_fft<float, double, float, 2>(L, Lw, w2, st) : run_fft<double, double, float, 2>(L, Lw, w2, st);
-    return big ? run_fft<float, float, float, 2>(L, Lw, w2, st) : run_fft<double, float, float, 2>(L, Lw, w2, st);
+        return big ? run_fft<float, double, float>(L, w2, nullptr, st) : run_fft<double, double, float>(L, w2, nullptr, st);
+    return big ? run_fft<float, float, float>(L, w2, nullptr, st) : run_fft<double, float, float>(L, w2, nullptr, st);
 }
 
 }  // namespace tfsc

@@ -3,7 +3,9 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_common import dev, lib, note
+import tfsc_inputs as ti
+from gpu_common import dev, gridspec, lib, note
+from oracle import transform as otf
 
 pytestmark = pytest.mark.gpu
 
@@ -30,3 +32,60 @@ def test_tile_max_at_block_and_table_edges(n, n_tiles, kind):
     np.minimum.at(rarg, tile[at], at)
     rarg[rarg == n] = -1
     assert np.array_equal(mx, rmx) and np.array_equal(arg, rarg)
+
+
+def _planes(store):
+    """The store's pixels as complex128 [C][K][Nt]."""
+    z = torch.view_as_complex(store.pix.to(torch.float64).contiguous())
+    z = {"layer": lambda v: v, "tranche": lambda v: v.transpose(1, 2), "layer_ci": lambda v: v.permute(2, 0, 1)}[store.layout](z)
+    if store.layer_scale is not None:
+        z = z * store.layer_scale.to(torch.float64)[:, :, None]
+    return z.cpu().numpy()
+
+
+@pytest.mark.parametrize("C, M, Nt", [(1, 64, 1), (2, 64, 257), (3, 128, 66), (2, 256, 63), (1, 512, 33), (3, 512, 17),
+                                      (2, 1024, 9), (1, 2048, 5), (2, 2048, 4), (2, 2048, 33), (3, 2048, 3), (2, 4096, 5)])
+@pytest.mark.parametrize("layout", ["layer", "tranche", "layer_ci"])
+def test_transform_at_tile_edges(C, M, Nt, layout):
+    """Every transform length (one to four exchanges, a remainder of none, one or two stages), tranche counts of one
+    tile more or less, every layout and channel count; white noise and a smooth PSD, so every pixel is of order 1.
+
+    Bounds, relative to the largest pixel: an FFT's error is below log2(M) roundings of each butterfly's operations (6,
+    at most 12 * 6 * u), u = 1.1e-16 in FP64 and 6e-8 in FP32 (M = 4096), plus one rounding of the stored value; the
+    16-bit grid adds half a step of 1/32767 of its layer's maximum."""
+    tfsc = lib()
+    g = ti.custom_grid(C, M, Nt, dt=5.0, modulated=False, gapped=False, cfg_id=11)
+    rng = np.random.default_rng(M + Nt)
+    x = rng.standard_normal((C, M * Nt))
+    K = M // 2 + 1
+    psd, mu = 1.0 + 0.5 * np.cos(np.arange(K) / K), 1.0 + 0.2 * rng.random(Nt)
+    keep = (rng.random(Nt) > 0.2).astype(np.uint8)
+    keep[-1] = 1
+    note(f"transform edges C={C} M={M} Nt={Nt} {layout}")
+    x32 = x.astype(np.float32)
+    for dtype, xx in (("f64", x), ("f32", x32), ("f32", x), ("i16", x32)):
+        if M == 4096 and dtype == "f64":
+            continue
+        st = tfsc.transform(gridspec(g), dev(xx), dev(psd), dev(mu), dev(keep), dtype=dtype, layout=layout)
+        ref, u, wm = otf.transform(xx.astype(np.float64), g, psd, mu, keep, 0.1, "rfft")
+        d = np.abs(_planes(st) - ref)
+        unit = 6e-8 if M == 4096 else 1.1e-16
+        bound = 72 * unit * np.abs(ref).max() + (0.0 if dtype == "f64" else 1.2e-7 * np.abs(ref).max())
+        if dtype == "i16":
+            bound = bound + 0.75 * np.maximum(np.abs(ref.real), np.abs(ref.imag)).max(axis=2, keepdims=True) / 32767.0
+        assert np.all(d <= bound), (dtype, float((d - bound).max()))
+        assert np.all(_planes(st)[:, :, keep == 0] == 0)
+
+
+def test_transform_into_a_store_off_16_bytes():
+    """An FP32 A+E store that starts 8 bytes off a 16-byte boundary holds the same bits as an aligned one."""
+    tfsc = lib()
+    g = ti.custom_grid(2, 256, 45, dt=5.0, modulated=False, gapped=False, cfg_id=11)
+    x = dev(np.random.default_rng(5).standard_normal((2, 256 * 45)).astype(np.float32))
+    args = (dev(np.ones(129)), dev(np.ones(45)), dev(np.ones(45, np.uint8)))
+    note("transform into an unaligned store")
+    a = tfsc.transform(gridspec(g), x, *args, dtype="f32", layout="layer_ci")
+    flat = torch.zeros(a.pix.numel() + 2, dtype=torch.float32, device="cuda")
+    b = tfsc.PixelStore(flat[2:].view_as(a.pix), torch.empty_like(a.inv_asd), torch.empty_like(a.tranche_w), "f32", "layer_ci")
+    tfsc.transform(gridspec(g), x, *args, dtype="f32", layout="layer_ci", out=b)
+    assert torch.equal(a.pix, b.pix) and float(flat[:2].abs().max()) == 0.0
