@@ -230,7 +230,11 @@ const char *tfsc_status_string(int status);
  * initialised; calls sharing one workspace must not overlap in time.  The
  * statistic and VJP figures include 8 bytes per template for a bank given
  * in ln Mc (the calls form exp(ln Mc) there once); an mc bank needs only
- * the geometry tables and 256 bytes, and the calls check that need.       */
+ * the geometry tables and 256 bytes, and the calls check that need.  The
+ * statistic's figure also holds optional scratch (at most 128 MiB) with
+ * which tfsc_bank_statistic shares out the tranches of small and medium
+ * banks over more waves; with a workspace that lacks it, it takes whole
+ * templates: the same results, bit for bit, later.                         */
 size_t tfsc_workspace_bytes(const tfsc_grid *grid, int64_t n_templates, const tfsc_options *opt, int which);
 
 /* Data -> TF pixels (paper Sec. "Implementation details": each tranche is

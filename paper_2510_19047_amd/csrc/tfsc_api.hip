@@ -130,11 +130,47 @@ size_t stat_ws_bytes(const tfsc_grid *g, int64_t n, bool log_mc) {
     return geo_bytes(g->n_tranches) + kAlign + (log_mc ? align_up(sizeof(double) * (size_t)n) : 0);
 }
 
-size_t ws_bytes_for(const tfsc_grid *g, int64_t n, int which) {
+// Scratch of split templates (tfsc_bank_statistic): records, units and chunk sums (elem: bytes of the arithmetic's type).
+// It lies behind the workspace above and is optional: a caller whose workspace holds no more than that gets whole
+// templates, and so does a bank that would take more than kSplitMost.
+constexpr size_t kSplitMost = 128u << 20;
+size_t split_bytes(int64_t n, const tfsc::SplitWs &s, size_t elem) {
+    if (!s.units) return 0;
+    return align_up(sizeof(double) * tfsc::kRecDoubles * (size_t)n) +
+           align_up(sizeof(tfsc::SplitUnit) * (size_t)n * (size_t)s.units) +
+           align_up(elem * 3 * (size_t)n * (size_t)s.n_chunks);
+}
+
+// The split of n templates at the default launch shape, or none.
+tfsc::SplitWs split_for(const tfsc_grid *g, int64_t n, size_t elem) {
+    tfsc::SplitWs s;
+    memset(&s, 0, sizeof(s));
+    tfsc::split_shape(n, g->n_tranches, (int64_t)device_cus() * 16, s);
+    if (split_bytes(n, s, elem) > kSplitMost) s.units = 0;
+    return s;
+}
+
+// Takes the split if the workspace has room for it.
+void use_split(const tfsc_grid *g, tfsc::StatLaunch &L, void *ws, size_t ws_bytes, bool log_mc) {
+    const size_t elem = L.precision == 0 ? sizeof(double) : sizeof(float);
+    tfsc::SplitWs s = split_for(g, L.n, elem);
+    const size_t base = stat_ws_bytes(g, L.n, log_mc);
+    if (!s.units || ws_bytes < base + split_bytes(L.n, s, elem)) return;
+    char *p = reinterpret_cast<char *>(ws) + base;
+    s.rec = reinterpret_cast<double *>(p);
+    p += align_up(sizeof(double) * tfsc::kRecDoubles * (size_t)L.n);
+    s.unit = reinterpret_cast<tfsc::SplitUnit *>(p);
+    p += align_up(sizeof(tfsc::SplitUnit) * (size_t)L.n * (size_t)s.units);
+    s.head = p;
+    L.split = s;
+}
+
+size_t ws_bytes_for(const tfsc_grid *g, int64_t n, int which, size_t elem = sizeof(double)) {
     switch (which) {
         case TFSC_WS_LAYOUT:
             return align_up(sizeof(int64_t) * (size_t)((n + 255) / 256 + 1));
         case TFSC_WS_STATISTIC:
+            return stat_ws_bytes(g, n, true) + split_bytes(n, split_for(g, n, elem), elem);
         case TFSC_WS_VJP:
             return stat_ws_bytes(g, n, true);
         case TFSC_WS_ORDER:
@@ -209,20 +245,8 @@ tfsc::StatLaunch stat_launch(const tfsc_grid *grid, const tfsc_pixels *pix, cons
     char *tail = reinterpret_cast<char *>(ws) + geo_bytes(grid->n_tranches);
     L.counter = reinterpret_cast<uint32_t *>(tail);
     L.u_scale = reinterpret_cast<const double *>(tail + tfsc::kTailScale);
-    if (bank->ln_mc) L.mc = reinterpret_cast<const double *>(tail + kAlign);  // filled by prepare_launch
+    if (bank->ln_mc) L.mc = reinterpret_cast<const double *>(tail + kAlign);  // filled by launch_prepare
     return L;
-}
-
-// Per-call tables the kernels read: the geometry of the orbit, the weight scale and, for a bank
-// given in ln Mc, the chirp masses.
-hipError_t prepare_launch(const tfsc_grid *grid, const tfsc_pixels *pix, const tfsc::StatLaunch &L, void *ws,
-                          hipStream_t st) {
-    hipError_t e = tfsc::launch_geometry(grid->n_tranches, (double)grid->tranche_len * grid->dt, pix->orbit,
-                                         reinterpret_cast<double *>(ws), st);
-    if (e != hipSuccess) return e;
-    e = tfsc::launch_weight_scale(grid->tranche_len / 2 + 1, pix->inv_asd, const_cast<double *>(L.u_scale), st);
-    if (e != hipSuccess || !L.ln_mc) return e;
-    return tfsc::launch_exp_mc(L.n, L.ln_mc, const_cast<double *>(L.mc), st);
 }
 
 }  // namespace
@@ -246,9 +270,8 @@ const char *tfsc_status_string(int s) {
 }
 
 size_t tfsc_workspace_bytes(const tfsc_grid *grid, int64_t n_templates, const tfsc_options *opt, int which) {
-    (void)opt;
     if (check_grid(grid) != TFSC_OK || n_templates < 0) return 0;
-    return ws_bytes_for(grid, n_templates, which);
+    return ws_bytes_for(grid, n_templates, which, opt && opt->precision == TFSC_F32 ? sizeof(float) : sizeof(double));
 }
 
 tfsc_status tfsc_segment_layout(const tfsc_grid *grid, const tfsc_bank *bank, tfsc_segments *seg, void *ws,
@@ -301,7 +324,9 @@ tfsc_status tfsc_bank_statistic(const tfsc_grid *grid, const tfsc_pixels *pix, c
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     if (bank->n == 0) return TFSC_OK;
     tfsc::StatLaunch L = stat_launch(grid, pix, bank, seg, r, ws);
-    if (prepare_launch(grid, pix, L, ws, st) != hipSuccess) return TFSC_ERR_HIP;
+    if (r.schedule == TFSC_SCHED_WAVE && r.fresnel == TFSC_FRESNEL_PAPER && !pix->links)
+        use_split(grid, L, ws, ws_bytes, bank->ln_mc != nullptr);
+    if (tfsc::launch_prepare(L, pix->orbit, st) != hipSuccess) return TFSC_ERR_HIP;
     L.seg_terms = seg_terms;
     L.stat = stat;
     L.seg_zn = seg_zn;
@@ -322,7 +347,7 @@ tfsc_status tfsc_bank_statistic_noalloc(const tfsc_grid *grid, const tfsc_pixels
     if (grid->n_tranches > TFSC_NOALLOC_MAX_TRANCHES || need > kScratchBytes) return TFSC_ERR_SCRATCH;
     void *ws = scratch_on_device();
     if (!ws) return TFSC_ERR_HIP;
-    return tfsc_bank_statistic(grid, pix, bank, seg, opt, seg_terms, stat, seg_zn, flags, n_active, ws, need,
+    return tfsc_bank_statistic(grid, pix, bank, seg, opt, seg_terms, stat, seg_zn, flags, n_active, ws, kScratchBytes,
                                stream);
 }
 
@@ -363,7 +388,7 @@ tfsc_status tfsc_bank_statistic_multi(const tfsc_grid *grid, const tfsc_pixels *
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     if (bank->n == 0) return TFSC_OK;
     tfsc::StatLaunch L = stat_launch(grid, pix, bank, seg, r, ws);
-    if (prepare_launch(grid, pix, L, ws, st) != hipSuccess) return TFSC_ERR_HIP;
+    if (tfsc::launch_prepare(L, pix->orbit, st) != hipSuccess) return TFSC_ERR_HIP;
     L.seg_terms = seg_terms;
     L.stat = stat;
     L.flags = flags;
@@ -412,7 +437,7 @@ tfsc_status tfsc_statistic_vjp(const tfsc_grid *grid, const tfsc_pixels *pix, co
     if (bank->n == 0) return TFSC_OK;
     tfsc::VjpLaunch V;
     V.s = stat_launch(grid, pix, bank, seg, r, ws);
-    if (prepare_launch(grid, pix, V.s, ws, st) != hipSuccess) return TFSC_ERR_HIP;
+    if (tfsc::launch_prepare(V.s, pix->orbit, st) != hipSuccess) return TFSC_ERR_HIP;
     V.seg_zn = seg_zn;
     V.g_stat = g_stat;
     V.g_seg = g_seg;
@@ -595,7 +620,7 @@ tfsc_status tfsc_bank_statistic_harmonics(const tfsc_grid *grid, const tfsc_pixe
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     if (bank->n == 0) return TFSC_OK;
     tfsc::StatLaunch L = stat_launch(grid, pix, bank, seg, r, ws);
-    if (prepare_launch(grid, pix, L, ws, st) != hipSuccess) return TFSC_ERR_HIP;
+    if (tfsc::launch_prepare(L, pix->orbit, st) != hipSuccess) return TFSC_ERR_HIP;
     L.seg_terms = seg_terms;
     L.stat = stat;
     L.seg_zn = seg_zn;

@@ -29,7 +29,6 @@ static hipError_t launch_acc_t(const StatLaunch &L, const StatArgs &a, hipStream
             hipLaunchKernelGGL((k_stat_thread_acc<C, R, PixT, 2>), grid, block, 0, st, a);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, st, a.counter, 1);
     const size_t shmem = sizeof(R) * ((size_t)a.K + 2 * kHalfBins);
     if (L.layout == 2)
         hipLaunchKernelGGL((k_stat_wave_acc<C, R, PixT, 2>), dim3(L.n_groups), dim3(64 * L.block_waves), shmem, st,

@@ -231,7 +231,6 @@ __global__ __launch_bounds__(256, 2) void k_stat_wave_harm(StatArgs a, HarmArgs 
 
 template <int C, class R, class PixT>
 static hipError_t launch_harm_t(const StatLaunch &L, const StatArgs &a, const HarmArgs &hm, hipStream_t st) {
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, st, a.counter, 1);
     const size_t shmem = sizeof(R) * ((size_t)a.K + 2 * kHalfBins);
     if (L.layout == 2)
         hipLaunchKernelGGL((k_stat_wave_harm<C, R, PixT, 2>), dim3(L.n_groups), dim3(64 * L.block_waves), shmem, st,

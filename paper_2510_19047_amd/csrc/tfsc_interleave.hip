@@ -234,7 +234,6 @@ __global__ __launch_bounds__(256, 3) void k_stat_wave_ri(StatArgs a) {
 
 template <int C, int NR, class PixT>
 static hipError_t launch_ri_t(const StatArgs &a, int n_groups, int block_waves, hipStream_t st) {
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, st, a.counter, 1);
     const size_t KP = (size_t)a.K + 2 * kHalfBins;
     const size_t shmem = sizeof(float) * KP * (PixTraits<PixT>::scaled ? 1 + NR * C : 1);
     hipLaunchKernelGGL((k_stat_wave_ri<C, NR, PixT>), dim3(n_groups), dim3(64 * block_waves), shmem, st, a);

@@ -28,6 +28,38 @@ struct LayoutLaunch {
     int64_t *block_sums;  // workspace, ceil(n / 256) entries
 };
 
+// Few templates: each template's chunks of 64 tranches are shared out in units of `chunks` of them, one unit per
+// wave (k_stat_split, k_vjp_split), and a finishing kernel joins the units.  units = 0: not split.
+constexpr int kSplitRun = 64;    // consecutive templates on one XCD (see run_item)
+constexpr int kRecDoubles = 32;  // doubles of a template record
+struct SplitUnit {
+    double zr, zi, N;  // sums of the segment that goes on into the next unit
+    int code, m_end;   // flag and tranche of the track's end, if it ends in the unit (m_end: else the unit's end)
+    int n_act, any;    // tranches with work; whether a segment closed in the unit has N > 0
+};
+struct SplitWs {
+    int n_chunks, chunks, units;  // chunks per template, per unit; units per template
+    double *rec;                  // [n][kRecDoubles]
+    void *head;                   // [n][n_chunks][3] of R: chunk sums of a segment that began in an earlier unit
+    SplitUnit *unit;              // [n][units]
+};
+
+// Chunks per unit and units per template for n templates of Nt tranches on n_waves waves (units = 0: whole templates).
+// Few templates leave waves idle, and up to some twenty a wave the units of a window, run together, also save reads behind
+// L2 (65,536 templates: 2.9 GB instead of 21.9).  Two-year grid, A+E, FP32, whole (one counter / runs) against split, us:
+// 1024: 645 / 537 / 270; 4099: 963 / 939 / 821; 16,000: 2831 / 2893 / 2572; 65,536: 10,035 / 9680 / 9290 (A+E+T 14,276 /
+// 12,594 / 11,067); 262,144: 36,703 / 34,960 / 34,740, where the records and sums would take 430 MB.  A wave gets up to
+// eight units, at least one chunk and at most 16 each: at 16,000 templates 12 chunks took 2572, 24 2592, 48 2767 us.
+inline void split_shape(int64_t n, int Nt, int64_t n_waves, SplitWs &s) {
+    s.n_chunks = (Nt + 63) / 64;
+    s.chunks = s.units = 0;
+    if (n < 1 || n > 20 * n_waves || s.n_chunks < 2) return;
+    const int64_t per = n * s.n_chunks / (8 * n_waves);
+    s.chunks = (int)(per < 1 ? 1 : (per > 16 ? 16 : per));
+    s.units = (s.n_chunks + s.chunks - 1) / s.chunks;
+    if (s.units < 2) s.units = 0;
+}
+
 struct StatLaunch {
     int M, Nt, C;
     double dt;
@@ -42,7 +74,7 @@ struct StatLaunch {
     const float *rho;       // [K][Nt] per-pixel weight factor, NULL for a separable PSD
     const double *links;    // [6][Nt] link light times (unequal arms), NULL for equal arms
     int tdi2;               // with links: second-generation TDI combinations
-    const double *u_scale;  // device scalar written by launch_weight_scale
+    const double *u_scale;  // device scalar written by launch_prepare
     int64_t n;
     const double *mc, *eta, *f0, *ct, *phi, *psi, *ci;
     const double *ln_mc;  // the bank given in ln Mc: the entry point fills mc (a workspace table) from it
@@ -58,6 +90,7 @@ struct StatLaunch {
     int64_t real_stride;  // bytes between realisation stores
     int64_t seg_stride;   // elements between realisation planes of seg_terms
     int multi_group;      // realisations sharing one pass over the bank: 1, 2, 4 or 8
+    SplitWs split;
 };
 
 constexpr int kMultiGroupDefault = 8;
@@ -117,15 +150,17 @@ struct TransformLaunch {
 };
 
 hipError_t launch_layout(const LayoutLaunch &L, hipStream_t st);
-hipError_t launch_geometry(int Nt, double dT, const double *orbit, double *geo, hipStream_t st);
+// What the statistic and VJP kernels read besides the caller's arrays, in one launch: the geometry tables (of the
+// analytic orbit or the caller's), the weight scale, the zeroed work counter, the chirp masses of a bank given in
+// ln Mc and, for split templates, their records (precision: that of the sky vectors).
+hipError_t launch_prepare(const StatLaunch &L, const double *orbit, hipStream_t st);
 hipError_t launch_orbit_positions(int Nt, double dT, double *out, hipStream_t st);
 hipError_t launch_link_lengths(int Nt, double dT, const double *orbit, double *out, hipStream_t st);
 hipError_t launch_statistic_interleaved(const StatLaunch &L, hipStream_t st);
 hipError_t launch_interleave(int64_t cells, int C, int K, int NR, int r, int elem_bytes, const void *src,
                              const float *src_scale, void *dst, float *dst_scale, hipStream_t st);
-hipError_t launch_exp_mc(int64_t n, const double *ln_mc, double *mc, hipStream_t st);
-hipError_t launch_weight_scale(int K, const double *inv_asd, double *scale_out, hipStream_t st);
 hipError_t launch_statistic(const StatLaunch &L, hipStream_t st);
+hipError_t launch_statistic_split(const StatLaunch &L, hipStream_t st);
 hipError_t launch_statistic_accurate(const StatLaunch &L, hipStream_t st);
 hipError_t launch_statistic_links(const StatLaunch &L, hipStream_t st);
 constexpr int kMaxHarmonics = 4;

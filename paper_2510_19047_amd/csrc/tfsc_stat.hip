@@ -216,27 +216,6 @@ __device__ inline void store_geometry(const double p[3][3], int m, int Nt, doubl
     }
 }
 
-// The analytic orbit at t_m = m dT.
-__global__ void k_geometry(int Nt, double dT, double *__restrict__ geo, float *__restrict__ geo32) {
-    int m = blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= Nt) return;
-    double p[3][3];
-    analytic_positions((double)m * dT, p);
-    store_geometry(p, m, Nt, geo, geo32);
-}
-
-// A caller's orbit: positions orbit[(3 i + x) Nt + m] of spacecraft i, coordinate x at t_m (light-seconds),
-// e.g. a numerical orbit; the arm vectors are formed from them as for the analytic orbit.
-__global__ void k_geometry_table(int Nt, const double *__restrict__ orbit, double *__restrict__ geo,
-                                 float *__restrict__ geo32) {
-    int m = blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= Nt) return;
-    double p[3][3];
-    for (int i = 0; i < 3; ++i)
-        for (int x = 0; x < 3; ++x) p[i][x] = orbit[(size_t)(3 * i + x) * Nt + m];
-    store_geometry(p, m, Nt, geo, geo32);
-}
-
 // The analytic orbit's positions in the caller's table layout [3 spacecraft][3 coordinates][Nt].
 __global__ void k_orbit_positions(int Nt, double dT, double *__restrict__ out) {
     int m = blockIdx.x * blockDim.x + threadIdx.x;
@@ -276,7 +255,7 @@ hipError_t launch_link_lengths(int Nt, double dT, const double *orbit, double *o
 // Exact power-of-two normalisation of the template weights: scale = 2^-e with e the
 // binary exponent of max_k u_k, so that max_k u_k * scale lies in [1/2, 1).  Upsilon is
 // invariant to it; it keeps |h u|^2 inside the FP32 range (u_k ~ 1e20 in strain units).
-__global__ void k_weight_scale(int K, const double *__restrict__ inv_asd, double *__restrict__ scale_out) {
+__device__ __forceinline__ void weight_scale(int K, const double *__restrict__ inv_asd, double *__restrict__ scale_out) {
     __shared__ double sh[256];
     // bins 1 .. K - 2 only: DC and Nyquist never enter the statistic
     double v = 0.0;
@@ -296,6 +275,59 @@ __global__ void k_weight_scale(int K, const double *__restrict__ inv_asd, double
         if (mx > 0.0) frexp(mx, &e);
         scale_out[0] = ldexp(1.0, -e);
     }
+}
+
+// The per-call tables (see launch_prepare), each by its own blocks of 256 threads: block 0 the weight scale and the work
+// counter, the next blocks the geometry (a tranche per thread: from the caller's positions orbit[(3 i + x) Nt + m] of
+// spacecraft i, coordinate x, in light-seconds, or from the analytic orbit), the last ones the templates (chirp mass and
+// record, a template per thread).  One launch instead of three or four: each is a few microseconds of latency.
+template <class R>
+__global__ __launch_bounds__(256) void k_prepare(StatArgs a, const double *__restrict__ ln_mc,
+                                                 const double *__restrict__ orbit, int geo_blocks) {
+    if (blockIdx.x == 0) {
+        if (threadIdx.x == 0) a.counter[0] = 0u;
+        weight_scale(a.K, a.inv_asd, const_cast<double *>(a.u_scale));
+        return;
+    }
+    if ((int)blockIdx.x <= geo_blocks) {
+        const int m = (blockIdx.x - 1) * 256 + threadIdx.x;
+        if (m >= a.Nt) return;
+        double p[3][3];
+        if (orbit) {
+            for (int i = 0; i < 3; ++i)
+                for (int x = 0; x < 3; ++x) p[i][x] = orbit[(size_t)(3 * i + x) * a.Nt + m];
+        } else {
+            analytic_positions((double)m * a.dT, p);
+        }
+        store_geometry(p, m, a.Nt, const_cast<double *>(a.geo), const_cast<float *>(a.geo32));
+        return;
+    }
+    const int64_t i = (int64_t)(blockIdx.x - 1 - geo_blocks) * 256 + threadIdx.x;
+    if (i >= a.n) return;
+    const double mc = ln_mc ? exp(ln_mc[i]) : a.mc[i];
+    if (ln_mc) const_cast<double *>(a.mc)[i] = mc;
+    if (!a.split.units) return;
+    double *rec = a.split.rec + i * kRecDoubles;
+    const bool ok = params_valid(mc, a.eta[i], a.f0[i], a.ct[i], a.ci[i]);
+    rec[kRecValid] = ok ? 1.0 : 0.0;
+    if (!ok) return;
+    Track T;
+    track_init(T, mc, a.eta[i], a.f0[i]);
+    Sky<R> S;
+    sky_init(S, a.ct[i], a.phi[i], a.psi[i], a.ci[i]);
+    record_fields(T, S, [&](int q, auto &x) { rec[q] = (double)x; });
+}
+
+hipError_t launch_prepare(const StatLaunch &L, const double *orbit, hipStream_t st) {
+    const StatArgs a = make_args(L);
+    const int geo_blocks = (L.Nt + 255) / 256;
+    const int64_t tmpl_blocks = L.ln_mc || L.split.units ? (L.n + 255) / 256 : 0;
+    const dim3 grid((unsigned)(1 + geo_blocks + tmpl_blocks));
+    if (L.precision == 0)
+        hipLaunchKernelGGL((k_prepare<double>), grid, dim3(256), 0, st, a, L.ln_mc, orbit, geo_blocks);
+    else
+        hipLaunchKernelGGL((k_prepare<float>), grid, dim3(256), 0, st, a, L.ln_mc, orbit, geo_blocks);
+    return hipGetLastError();
 }
 
 __global__ void k_zero_u32(uint32_t *p, int n) {
@@ -630,15 +662,6 @@ hipError_t launch_layout(const LayoutLaunch &L, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_geometry(int Nt, double dT, const double *orbit, double *geo, hipStream_t st) {
-    if (orbit)
-        hipLaunchKernelGGL(k_geometry_table, dim3((Nt + 127) / 128), dim3(128), 0, st, Nt, orbit, geo,
-                           geo32_of(geo, Nt));
-    else
-        hipLaunchKernelGGL(k_geometry, dim3((Nt + 127) / 128), dim3(128), 0, st, Nt, dT, geo, geo32_of(geo, Nt));
-    return hipGetLastError();
-}
-
 hipError_t launch_orbit_positions(int Nt, double dT, double *out, hipStream_t st) {
     hipLaunchKernelGGL(k_orbit_positions, dim3((Nt + 127) / 128), dim3(128), 0, st, Nt, dT, out);
     return hipGetLastError();
@@ -666,9 +689,9 @@ static hipError_t launch_thread_t(const StatArgs &a, int layout, hipStream_t st)
     return hipGetLastError();
 }
 
+// The counter is zero (k_prepare).
 template <int C, class R, class PixT>
 static hipError_t launch_wave_t(const StatArgs &a, int layout, int n_groups, int block_waves, hipStream_t st) {
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, st, a.counter, 1);
     const size_t KP = (size_t)a.K + 2 * kHalfBins;
     size_t shmem = sizeof(R) * KP + (PixTraits<PixT>::scaled ? sizeof(float) * C * KP : 0);
     if constexpr (!PixTraits<PixT>::scaled) {
@@ -724,23 +747,6 @@ static hipError_t dispatch_pix(const StatLaunch &L, const StatArgs &a, hipStream
                 return hipErrorInvalidValue;
     }
     return hipErrorInvalidValue;
-}
-
-// Chirp masses of a bank given in ln Mc, formed once per call for the statistic and VJP kernels.
-__global__ void k_exp_mc(int64_t n, const double *__restrict__ ln_mc, double *__restrict__ mc) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) mc[i] = exp(ln_mc[i]);
-}
-
-hipError_t launch_exp_mc(int64_t n, const double *ln_mc, double *mc, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_exp_mc, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, ln_mc, mc);
-    return hipGetLastError();
-}
-
-hipError_t launch_weight_scale(int K, const double *inv_asd, double *scale_out, hipStream_t st) {
-    hipLaunchKernelGGL(k_weight_scale, dim3(1), dim3(256), 0, st, K, inv_asd, scale_out);
-    return hipGetLastError();
 }
 
 template <int C, class R, int RR>
@@ -806,6 +812,7 @@ hipError_t launch_statistic_multi(const StatLaunch &L, hipStream_t st) {
 hipError_t launch_statistic(const StatLaunch &L, hipStream_t st) {
     StatArgs a = make_args(L);
     if (L.n == 0) return hipSuccess;
+    if (L.split.units || (L.schedule == 1 && L.order)) return launch_statistic_split(L, st);
     if (L.C == 1) return L.precision == 0 ? dispatch_pix<1, double>(L, a, st) : dispatch_pix<1, float>(L, a, st);
     if (L.C == 3) return L.precision == 0 ? dispatch_pix<3, double>(L, a, st) : dispatch_pix<3, float>(L, a, st);
     return L.precision == 0 ? dispatch_pix<2, double>(L, a, st) : dispatch_pix<2, float>(L, a, st);

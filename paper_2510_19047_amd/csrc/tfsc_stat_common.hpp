@@ -23,7 +23,7 @@ struct StatArgs {
     const double *tranche_w;
     const double *geo;
     const float *geo32;
-    const double *u_scale;  // [1], see k_weight_scale
+    const double *u_scale;  // [1], see weight_scale
     const float *rho;       // [K][Nt] per-pixel weight factor (general per-tranche PSD), else NULL
     uint32_t rho_bytes;
     const double *links;    // [6][Nt] link light times (unequal arms), else NULL
@@ -42,6 +42,7 @@ struct StatArgs {
     uint32_t real_stride;
     int64_t seg_stride;
     int rho0;  // first realisation of this launch
+    SplitWs split;  // templates cut into units of chunks (k_stat_split)
 };
 
 // Chirp mass of template i: from the bank's mc, or exp(ln Mc) when the bank is given in ln Mc (the
@@ -92,6 +93,16 @@ struct SegWalk {
         lo = 0;
         qs = q;
         rs = r;
+        hi = qs + (rs > 0 ? 1 : 0);
+    }
+    // at the segment that holds tranche m
+    __device__ __forceinline__ void init_at(int Nt, int nseg, int m) {
+        init(Nt, nseg);
+        s = (int)((int64_t)m * nseg / Nt);
+        const int64_t a = (int64_t)s * Nt, b = a + Nt;
+        lo = (int)((a + nseg - 1) / nseg);
+        qs = (int)(b / nseg);
+        rs = (int)(b - (int64_t)qs * nseg);
         hi = qs + (rs > 0 ? 1 : 0);
     }
     __device__ __forceinline__ void step() {
@@ -602,6 +613,62 @@ __device__ __forceinline__ void wave_uniform(Sky<R> &S) {
     S.q = wave_uniform(S.q);
 }
 
+// ------------------------------------------------------------------ work in runs per XCD
+// The place in the processing order that a wave of a grid of run_groups blocks takes (n or more: none), and its unit.
+// All templates of a unit come before the next unit.  Within it XCD x (blocks go round the 8 XCDs) takes every eighth run
+// of kSplitRun templates in processing order: the waves that run together on an XCD read neighbouring rows of the same
+// time, which its L2 then holds, and long and short tracks are spread over the XCDs.
+__device__ __forceinline__ int64_t run_item(int64_t n, int &unit) {
+    const uint32_t w = blockDim.x >> 6, run = kSplitRun / w;  // blocks per run (w is 1 to 4)
+    const uint32_t len = 8 * run * w, per = (uint32_t)((n + len - 1) / len) * run;  // blocks per XCD and unit
+    const uint32_t j = (blockIdx.x >> 3) % per;
+    unit = (int)((blockIdx.x >> 3) / per);
+    return ((int64_t)(j / run) * 8 + (blockIdx.x & 7)) * (run * w) + (j % run) * w +
+           __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+}
+
+inline unsigned run_groups(int64_t n, int block_waves, int units) {
+    const int run = kSplitRun / block_waves, len = 8 * run * block_waves;
+    return (unsigned)((n + len - 1) / len * 8 * run * units);
+}
+
+// ------------------------------------------------------------------ template records
+// A template's constants as k_prepare writes them for the split kernels: kRecDoubles doubles, the Track, the FP64
+// propagation direction, the sky vectors (values of R) and 1.0 if its parameters are valid.
+__device__ __forceinline__ double lane_double(double v, int l) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)b, l);
+    const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), l);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+template <class R, class F>
+__device__ __forceinline__ void record_fields(Track &T, Sky<R> &S, F &&f) {
+    double *const t[17] = {&T.eta, &T.M,  &T.c8,  &T.a2,  &T.a3,  &T.a4,  &T.b2,   &T.b3,  &T.b4,
+                           &T.tc,  &T.th0, &T.M5, &T.M40, &T.r5M, &T.rc8, &T.r40M, &T.reta};
+#pragma unroll
+    for (int q = 0; q < 17; ++q) f(q, *t[q]);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        f(17 + q, S.kd[q]);
+        f(20 + q, S.k[q]);
+        f(23 + q, S.u[q]);
+        f(26 + q, S.v[q]);
+    }
+    f(29, S.q);
+}
+constexpr int kRecValid = 30;
+static_assert(kRecValid < kRecDoubles, "record size");
+
+// One load of the record by the wave's lanes, then every field as a wave-uniform value; false: invalid parameters.
+template <class R>
+__device__ __forceinline__ bool load_record(const double *__restrict__ rec, int lane, Track &T, Sky<R> &S) {
+    const double v = rec[lane & (kRecDoubles - 1)];
+    if (lane_double(v, kRecValid) == 0.0) return false;
+    record_fields(T, S, [&](int q, auto &x) { x = lane_double(v, q); });
+    return true;
+}
+
 // ------------------------------------------------------------------ THREAD schedule
 // The body of the thread-per-template kernels (k_stat_thread; the accurate-Fresnel variant).
 template <int C, class R, class PixT, int LAYOUT, bool RHO, int FR, bool LK = false>
@@ -661,11 +728,16 @@ __device__ __forceinline__ void stat_thread_body(const StatArgs &a) {
 }
 
 // The body of the wave-per-template kernels (k_stat_wave; the accurate-Fresnel variant, which takes the
-// general form on all 21 bins; the unequal-arm variant, LK).
-template <int C, class R, class PixT, int LAYOUT, bool RHO, int FR, bool LK = false>
+// general form on all 21 bins; the unequal-arm variant, LK) and of its forms with one item per wave: kRuns, whole
+// templates in runs per XCD (k_stat_runs), and kUnits, some consecutive 64-tranche chunks of a template (k_stat_split).
+// The arithmetic of a chunk is the same in all.
+enum : int { kCounter = 0, kRuns = 1, kUnits = 2 };
+
+template <int C, class R, class PixT, int LAYOUT, bool RHO, int FR, bool LK = false, int FETCH = kCounter>
 __device__ __forceinline__ void stat_wave_body(const StatArgs &a) {
     // Zero-padded template weights u_pad[k + 10] = u_k for 1 <= k <= M/2 - 1 (else 0), and
     // the 16-bit layer scales, staged in LDS once per block.
+    constexpr bool SPLIT = FETCH == kUnits, ONE = FETCH != kCounter;
     extern __shared__ unsigned char smem_raw[];
     const int KP = a.K + 2 * kHalfBins;
     R *u_pad = reinterpret_cast<R *>(smem_raw);
@@ -688,45 +760,67 @@ __device__ __forceinline__ void stat_wave_body(const StatArgs &a) {
 
     const int lane = threadIdx.x & 63;
     for (;;) {
-        // Work fetch in converged code: every lane joins one atomic on a uniform address
-        // (lane 0 adds 1, the others 0), which the compiler turns into a single atomic per
-        // wave, and readfirstlane makes the item a wave-uniform scalar, so no cross-lane
-        // broadcast depends on reconvergence after a lane-0-only branch.
-        const uint32_t mine = atomicAdd(a.counter, lane == 0 ? 1u : 0u);
-        const int64_t item = (int64_t)__builtin_amdgcn_readfirstlane(mine);
-        if (item >= a.n) break;
+        int64_t item;
+        int unit = 0;
+        if constexpr (ONE) {
+            item = run_item(a.n, unit);
+            if (item >= a.n) break;
+        } else {
+            // Work fetch in converged code: every lane joins one atomic on a uniform address
+            // (lane 0 adds 1, the others 0), which the compiler turns into a single atomic per
+            // wave, and readfirstlane makes the item a wave-uniform scalar, so no cross-lane
+            // broadcast depends on reconvergence after a lane-0-only branch.
+            const uint32_t mine = atomicAdd(a.counter, lane == 0 ? 1u : 0u);
+            item = (int64_t)__builtin_amdgcn_readfirstlane(mine);
+            if (item >= a.n) break;
+        }
         const int64_t i = a.order ? (int64_t)__builtin_amdgcn_readfirstlane(a.order[item]) : item;
-        if (i < 0 || i >= a.n) continue;  // malformed processing order: skip rather than fault
+        if (i < 0 || i >= a.n) {  // malformed processing order: skip rather than fault
+            if constexpr (ONE) break;
+            continue;
+        }
         const int ns = a.nseg[i];
         const int64_t off = a.seg_offset[i];
         SegAcc<double> acc{0, 0, 0, 0, 0, false};
         int flag = 0;
         const bool writer = lane == 0;
-        if (!params_valid(a.mc[i], a.eta[i], a.f0[i], a.ct[i], a.ci[i])) {
+        Track T;
+        Sky<R> S;
+        if constexpr (SPLIT) {
+            if (!load_record(a.split.rec + i * kRecDoubles, lane, T, S)) break;  // k_stat_finish fills in its outputs
+        } else if (!params_valid(a.mc[i], a.eta[i], a.f0[i], a.ct[i], a.ci[i])) {
             close_segments(acc, ns, off, a.seg_terms, a.seg_zn, writer);
             if (writer) {
                 a.stat[i] = 0.0;
                 a.flags[i] = kFlagInvalid;
                 if (a.n_active) a.n_active[i] = 0;
             }
+            if constexpr (ONE) break;
             continue;
+        } else {
+            track_init(T, a.mc[i], a.eta[i], a.f0[i]);
+            wave_uniform(T);
+            sky_init(S, a.ct[i], a.phi[i], a.psi[i], a.ci[i]);
+            wave_uniform(S);
         }
-        Track T;
-        track_init(T, a.mc[i], a.eta[i], a.f0[i]);
-        wave_uniform(T);
-        Sky<R> S;
-        sky_init(S, a.ct[i], a.phi[i], a.psi[i], a.ci[i]);
-        wave_uniform(S);
-        int m_end = a.Nt, n_act = 0;
+        const int m_beg = SPLIT ? unit * a.split.chunks * 64 : 0;
+        const int m_stop = SPLIT ? min(a.Nt, m_beg + a.split.chunks * 64) : a.Nt;
+        int m_end = m_stop, n_act = 0;
         SegWalk sw;
-        sw.init(a.Nt, ns);
+        if constexpr (SPLIT)
+            sw.init_at(a.Nt, ns, m_beg);
+        else
+            sw.init(a.Nt, ns);
+        // SPLIT: the segment that began in an earlier unit keeps its chunks' sums apart
+        const int head_seg = SPLIT && sw.lo < m_beg ? sw.s : -1;
+        if constexpr (SPLIT) acc.cur = head_seg >= 0 ? sw.s + 1 : sw.s;
         // The track of a chunk is evaluated during the previous chunk, in the same block as that chunk's
         // response, so the dependent FP64 chain and the FP32 response fill each other's issue gaps.
         double Phi, f, fdot;
-        int code = track_step_lanes(T, (double)(lane < a.Nt ? lane : a.Nt - 1) * a.dT, a.dT, a.df, a.fnyq, Phi, f,
-                                    fdot);
-        code = lane < a.Nt ? code : 0;
-        for (int m0 = 0; m0 < m_end; m0 += 64) {
+        const int mf = m_beg + lane;
+        int code = track_step_lanes(T, (double)(mf < a.Nt ? mf : a.Nt - 1) * a.dT, a.dT, a.df, a.fnyq, Phi, f, fdot);
+        code = mf < a.Nt ? code : 0;
+        for (int m0 = m_beg; m0 < m_end; m0 += 64) {
             const int m = m0 + lane;
             const bool inr = m < a.Nt;
             const double wm_raw = inr ? a.tranche_w[m] : 0.0;
@@ -789,15 +883,40 @@ __device__ __forceinline__ void stat_wave_body(const StatArgs &a) {
                     const bool mine = active && m >= sw.lo && m < sw.hi;
                     R vr = mine ? zr : (R)0, vi = mine ? zi : (R)0, vn = mine ? nn : (R)0;
                     wave_sum3<R>(vr, vi, vn);
-                    close_segments(acc, sw.s, off, a.seg_terms, a.seg_zn, writer);
-                    acc.zr += (double)vr;
-                    acc.zi += (double)vi;
-                    acc.N += (double)vn;
+                    if (SPLIT && sw.s == head_seg) {
+                        if (writer) {
+                            R *h = reinterpret_cast<R *>(a.split.head) + (i * a.split.n_chunks + (m0 >> 6)) * 3;
+                            h[0] = vr;
+                            h[1] = vi;
+                            h[2] = vn;
+                        }
+                    } else {
+                        close_segments(acc, sw.s, off, a.seg_terms, a.seg_zn, writer);
+                        acc.zr += (double)vr;
+                        acc.zi += (double)vi;
+                        acc.N += (double)vn;
+                    }
                     if (sw.hi > last) break;
                     sw.step();
                 }
             }
             if (viol) break;
+        }
+        if constexpr (SPLIT) {
+            // segments that end in the unit are closed; of the one that goes on, the sums so far are kept
+            close_segments(acc, m_stop < a.Nt ? (int)((int64_t)m_stop * ns / a.Nt) : ns, off, a.seg_terms, a.seg_zn,
+                           writer);
+            if (writer) {
+                SplitUnit *o = a.split.unit + (i * a.split.units + unit);
+                o->zr = acc.zr;
+                o->zi = acc.zi;
+                o->N = acc.N;
+                o->code = flag;
+                o->m_end = m_end;
+                o->n_act = n_act;
+                o->any = acc.any;
+            }
+            break;
         }
         if (m_end == 0) flag |= kFlagEmpty;
         close_segments(acc, ns, off, a.seg_terms, a.seg_zn, writer);
@@ -807,6 +926,7 @@ __device__ __forceinline__ void stat_wave_body(const StatArgs &a) {
             a.flags[i] = flag;
             if (a.n_active) a.n_active[i] = n_act;
         }
+        if constexpr (ONE) break;
     }
 }
 
@@ -859,6 +979,7 @@ inline StatArgs make_args(const StatLaunch &L) {
     a.real_stride = 0;
     a.seg_stride = 0;
     a.rho0 = 0;
+    a.split = L.split;
     return a;
 }
 

@@ -737,10 +737,6 @@ __global__ __launch_bounds__(256, sizeof(R) == 4 ? 2 : 1) void k_vjp_wave(VjpArg
     }
 }
 
-__global__ void k_vjp_zero(uint32_t *counter) {
-    if (threadIdx.x == 0) counter[0] = 0u;
-}
-
 template <int C, class PixT, class R>
 static hipError_t launch_vjp_t(const VjpArgs &a, int n_groups, int block_waves, hipStream_t st) {
     const size_t shmem = sizeof(R) * ((size_t)a.K + 2 * kHalfBins);
@@ -804,7 +800,6 @@ hipError_t launch_vjp(const VjpLaunch &V, hipStream_t st) {
     const int bw = L.block_waves;
     int64_t groups = (L.n + bw - 1) / bw;
     if (groups > (int64_t)L.n_groups) groups = L.n_groups;
-    hipLaunchKernelGGL(k_vjp_zero, dim3(1), dim3(64), 0, st, a.counter);
     return L.precision == 1 ? dispatch_vjp_c<float>(a, L.C, L.pix_dtype, (int)groups, bw, st)
                             : dispatch_vjp_c<double>(a, L.C, L.pix_dtype, (int)groups, bw, st);
 }

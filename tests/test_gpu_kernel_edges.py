@@ -4,7 +4,7 @@ import pytest
 import torch
 
 import tfsc_inputs as ti
-from gpu_common import dev, gridspec, lib, note
+from gpu_common import dev, gridspec, lib, note, small_data, store_from_oracle
 from oracle import transform as otf
 
 pytestmark = pytest.mark.gpu
@@ -89,3 +89,65 @@ def test_transform_into_a_store_off_16_bytes():
     b = tfsc.PixelStore(flat[2:].view_as(a.pix), torch.empty_like(a.inv_asd), torch.empty_like(a.tranche_w), "f32", "layer_ci")
     tfsc.transform(gridspec(g), x, *args, dtype="f32", layout="layer_ci", out=b)
     assert torch.equal(a.pix, b.pix) and float(flat[:2].abs().max()) == 0.0
+
+
+def _bank(tfsc, n, seed):
+    b = ti.random_bank(n, seed, mc_range=(5.0, 100.0), f0_range=(0.004, 0.08), eta=None, stream=62)
+    if n > 20:
+        b.mc[3], b.eta[5], b.f0[7], b.cos_iota[9] = -2.0, 0.3, 0.2, 1.0  # invalid, invalid, empty track, face-on
+    return tfsc.BankTensors.from_host(b)
+
+
+def _all_equal(a, b):
+    for k in ("stat", "seg_terms", "seg_zn", "flags", "n_active"):
+        x, y = getattr(a, k), getattr(b, k)
+        assert torch.equal(x, y), (k, int((x != y).sum()))
+
+
+@pytest.mark.parametrize("nseg", [0, 1, 7, 8, 1000])
+@pytest.mark.parametrize("precision", ["f32", "f64"])
+def test_split_templates_equal_whole_ones(precision, nseg):
+    """Chunks shared out over the waves (a workspace with room for it) against whole templates (the static scratch
+    has none for this bank), bit for bit: segments inside a unit, across units, shorter than a tranche, tracks that
+    end in every part of the grid, invalid and empty templates, excluded tranches."""
+    tfsc = lib()
+    d = small_data()
+    g = gridspec(d["grid"])
+    store = store_from_oracle(d, precision, "layer_ci")
+    for n in (5000, 1):
+        bank = _bank(tfsc, n, 13)
+        seg = tfsc.segment_layout(g, bank, nseg)
+        order = tfsc.processing_order(g, bank)
+        note(f"split against whole templates: {precision} nseg={nseg} n={n}")
+        for o in (order, None):
+            a = tfsc.bank_statistic(g, store, bank, seg, precision=precision, want_zn=True, want_active=True, order=o)
+            b = tfsc.bank_statistic_noalloc(g, store, bank, seg, precision=precision, want_zn=True, want_active=True,
+                                            order=o)
+            _all_equal(a, b)
+
+
+@pytest.mark.parametrize("block_waves", [1, 3, 4])
+def test_runs_of_the_processing_order_equal_the_counter(block_waves):
+    """A bank too large to split: one wave per template in runs per XCD (with a processing order) against the work
+    counter (without), bit for bit, with an order whose last entries are out of range (those templates are left out)."""
+    tfsc = lib()
+    g = ti.custom_grid(2, 64, 130, dt=5.0, modulated=False, gapped=False, cfg_id=11)
+    rng = np.random.default_rng(3)
+    z = rng.standard_normal((2, 33, 130)) + 1j * rng.standard_normal((2, 33, 130))
+    store = tfsc.PixelStore.from_complex(dev(z), dev(np.ones(33)), dev(np.ones(130)), "f32", "layer_ci")
+    grid = gridspec(g)
+    bank = _bank(tfsc, 100_003, 17)
+    seg = tfsc.segment_layout(grid, bank)
+    order = tfsc.processing_order(grid, bank)
+    note(f"runs against the counter: block_waves={block_waves}")
+    kw = dict(precision="f32", want_zn=True, want_active=True, block_waves=block_waves)
+    a = tfsc.bank_statistic(grid, store, bank, seg, order=order, **kw)
+    b = tfsc.bank_statistic(grid, store, bank, seg, **kw)
+    _all_equal(a, b)
+    left = order[-2:].long()
+    short = order.clone()
+    short[-2:] = torch.tensor([-1, 100_003], dtype=torch.int32, device="cuda")
+    a.stat[left] = -1.0
+    tfsc.bank_statistic(grid, store, bank, seg, order=short, out=a, **kw)
+    b.stat[left] = -1.0
+    assert torch.equal(a.stat, b.stat)
