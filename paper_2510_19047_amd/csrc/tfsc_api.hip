@@ -165,14 +165,40 @@ void use_split(const tfsc_grid *g, tfsc::StatLaunch &L, void *ws, size_t ws_byte
     L.split = s;
 }
 
+// The same for the VJP: records and the units' gradients.  Its kernel runs two waves per SIMD (FP32 arithmetic) or one.
+tfsc::SplitWs vjp_split_for(const tfsc_grid *g, int64_t n, size_t elem) {
+    tfsc::SplitWs s;
+    memset(&s, 0, sizeof(s));
+    tfsc::split_shape(n, g->n_tranches, (int64_t)device_cus() * (elem == sizeof(double) ? 4 : 8), s, 40);
+    return s;
+}
+
+size_t vjp_split_bytes(int64_t n, const tfsc::SplitWs &s) {
+    if (!s.units) return 0;
+    return align_up(sizeof(double) * tfsc::kRecDoubles * (size_t)n) +
+           align_up(sizeof(double) * 5 * (size_t)n * (size_t)s.units);
+}
+
+void use_vjp_split(const tfsc_grid *g, tfsc::StatLaunch &L, void *ws, size_t ws_bytes, bool log_mc) {
+    tfsc::SplitWs s = vjp_split_for(g, L.n, L.precision == 0 ? sizeof(double) : sizeof(float));
+    const size_t base = stat_ws_bytes(g, L.n, log_mc), need = vjp_split_bytes(L.n, s);
+    if (!s.units || need > kSplitMost || ws_bytes < base + need) return;
+    char *p = reinterpret_cast<char *>(ws) + base;
+    s.rec = reinterpret_cast<double *>(p);
+    s.head = p + align_up(sizeof(double) * tfsc::kRecDoubles * (size_t)L.n);
+    L.split = s;
+}
+
 size_t ws_bytes_for(const tfsc_grid *g, int64_t n, int which, size_t elem = sizeof(double)) {
     switch (which) {
         case TFSC_WS_LAYOUT:
             return align_up(sizeof(int64_t) * (size_t)((n + 255) / 256 + 1));
         case TFSC_WS_STATISTIC:
             return stat_ws_bytes(g, n, true) + split_bytes(n, split_for(g, n, elem), elem);
-        case TFSC_WS_VJP:
-            return stat_ws_bytes(g, n, true);
+        case TFSC_WS_VJP: {
+            const size_t b = vjp_split_bytes(n, vjp_split_for(g, n, elem));
+            return stat_ws_bytes(g, n, true) + (b > kSplitMost ? 0 : b);
+        }
         case TFSC_WS_ORDER:
         {
             const size_t nb = (size_t)(g->tranche_len / 2 + 1) * tfsc::kOrderMcClasses + 1;
@@ -437,6 +463,7 @@ tfsc_status tfsc_statistic_vjp(const tfsc_grid *grid, const tfsc_pixels *pix, co
     if (bank->n == 0) return TFSC_OK;
     tfsc::VjpLaunch V;
     V.s = stat_launch(grid, pix, bank, seg, r, ws);
+    use_vjp_split(grid, V.s, ws, ws_bytes, bank->ln_mc != nullptr);
     if (tfsc::launch_prepare(V.s, pix->orbit, st) != hipSuccess) return TFSC_ERR_HIP;
     V.seg_zn = seg_zn;
     V.g_stat = g_stat;

@@ -44,16 +44,17 @@ struct SplitWs {
     SplitUnit *unit;              // [n][units]
 };
 
-// Chunks per unit and units per template for n templates of Nt tranches on n_waves waves (units = 0: whole templates).
+// Chunks per unit and units per template for n templates of Nt tranches on n_waves waves, if there are at most `most`
+// templates a wave (units = 0: whole templates).
 // Few templates leave waves idle, and up to some twenty a wave the units of a window, run together, also save reads behind
 // L2 (65,536 templates: 2.9 GB instead of 21.9).  Two-year grid, A+E, FP32, whole (one counter / runs) against split, us:
 // 1024: 645 / 537 / 270; 4099: 963 / 939 / 821; 16,000: 2831 / 2893 / 2572; 65,536: 10,035 / 9680 / 9290 (A+E+T 14,276 /
 // 12,594 / 11,067); 262,144: 36,703 / 34,960 / 34,740, where the records and sums would take 430 MB.  A wave gets up to
 // eight units, at least one chunk and at most 16 each: at 16,000 templates 12 chunks took 2572, 24 2592, 48 2767 us.
-inline void split_shape(int64_t n, int Nt, int64_t n_waves, SplitWs &s) {
+inline void split_shape(int64_t n, int Nt, int64_t n_waves, SplitWs &s, int most = 20) {
     s.n_chunks = (Nt + 63) / 64;
     s.chunks = s.units = 0;
-    if (n < 1 || n > 20 * n_waves || s.n_chunks < 2) return;
+    if (n < 1 || n > most * n_waves || s.n_chunks < 2) return;
     const int64_t per = n * s.n_chunks / (8 * n_waves);
     s.chunks = (int)(per < 1 ? 1 : (per > 16 ? 16 : per));
     s.units = (s.n_chunks + s.chunks - 1) / s.chunks;

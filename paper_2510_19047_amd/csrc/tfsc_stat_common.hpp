@@ -660,6 +660,15 @@ __device__ __forceinline__ void record_fields(Track &T, Sky<R> &S, F &&f) {
 constexpr int kRecValid = 30;
 static_assert(kRecValid < kRecDoubles, "record size");
 
+// The record's track alone (the VJP kernels).
+__device__ __forceinline__ void load_track(const double *__restrict__ rec, int lane, Track &T) {
+    const double v = rec[lane & (kRecDoubles - 1)];
+    Sky<double> unused;
+    record_fields(T, unused, [&](int q, auto &x) {
+        if (q < 17) x = lane_double(v, q);
+    });
+}
+
 // One load of the record by the wave's lanes, then every field as a wave-uniform value; false: invalid parameters.
 template <class R>
 __device__ __forceinline__ bool load_record(const double *__restrict__ rec, int lane, Track &T, Sky<R> &S) {

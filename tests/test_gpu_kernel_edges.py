@@ -151,3 +151,31 @@ def test_runs_of_the_processing_order_equal_the_counter(block_waves):
     tfsc.bank_statistic(grid, store, bank, seg, order=short, out=a, **kw)
     b.stat[left] = -1.0
     assert torch.equal(a.stat, b.stat)
+
+
+@pytest.mark.parametrize("C, layout, dtype", [(1, "layer", "f32"), (2, "layer_ci", "f32"), (3, "tranche", "f64")])
+@pytest.mark.parametrize("precision", ["f32", "f64"])
+def test_vjp_units_equal_whole_templates(C, layout, dtype, precision):
+    """The VJP with a template's chunks shared out (5003 templates) against whole templates (the same ones in a bank of
+    90,000, which is not split): equal but for the order of the FP64 sum over the tranches, at most 130 terms of at most
+    1e3 times the largest gradient, so below 130 * 1.1e-16 * 1e3 = 1.5e-11 of it; 1e-9 is asked for."""
+    tfsc = lib()
+    M, Nt = 64, 130
+    g = ti.custom_grid(C, M, Nt, dt=5.0, modulated=False, gapped=False, cfg_id=11)
+    grid = gridspec(g)
+    rng = np.random.default_rng(5)
+    z = rng.standard_normal((C, M // 2 + 1, Nt)) + 1j * rng.standard_normal((C, M // 2 + 1, Nt))
+    wm = np.where(rng.random(Nt) > 0.1, 1.0, 0.0)
+    store = tfsc.PixelStore.from_complex(dev(z), dev(np.ones(M // 2 + 1)), dev(wm), dtype, layout)
+    big = _bank(tfsc, 90_003, 19)
+    few = tfsc.BankTensors(*(getattr(big, k)[:5003].contiguous() for k in tfsc.BankTensors.FIELDS))
+    note(f"VJP units against whole templates: C={C} {layout} {dtype} {precision}")
+    out = []
+    for bank in (big, few):
+        seg = tfsc.segment_layout(grid, bank, 3)
+        zn = torch.as_tensor(np.random.default_rng(6).standard_normal((90_003 * 3, 3)), device="cuda")[: 3 * bank.n].abs()
+        out.append(tfsc.statistic_vjp(grid, store, bank, seg, zn.contiguous(),
+                                      g_stat=torch.ones(bank.n, dtype=torch.float64, device="cuda"), precision=precision))
+    a, b = out[0][:5003], out[1]
+    assert torch.isfinite(b).all()
+    assert float(((a - b).abs() / a.abs().amax(dim=0)).max()) < 1e-9
