@@ -73,6 +73,9 @@ __device__ __forceinline__ void close_segments_ri(SegAccRi<NR> &acc, int upto, i
     }
 }
 
+// Bound: the memory behind L2 beside vector-ALU issue.  262,144 templates of the wide bank, two realisations, two-year grid
+// (with the two transforms): 63.3 ms from the work counter, 47.0 ms in runs of the processing order per XCD, whose L2s
+// then hold the rows that neighbouring templates share.
 template <int C, int NR, class PixT>
 __global__ __launch_bounds__(256, 3) void k_stat_wave_ri(StatArgs a) {
 #pragma clang fp contract(fast)
@@ -98,13 +101,22 @@ __global__ __launch_bounds__(256, 3) void k_stat_wave_ri(StatArgs a) {
     const GeoView gv = geo_view(a.geo, a.geo32, a.Nt);
     const int lane = threadIdx.x & 63;
     const bool writer = lane == 0;
-    for (;;) {
-        // one atomic per wave on a uniform address, as in k_stat_wave
-        const uint32_t mine = atomicAdd(a.counter, lane == 0 ? 1u : 0u);
-        const int64_t item = (int64_t)__builtin_amdgcn_readfirstlane(mine);
-        if (item >= a.n) break;
-        const int64_t i = a.order ? (int64_t)__builtin_amdgcn_readfirstlane(a.order[item]) : item;
-        if (i < 0 || i >= a.n) continue;  // malformed processing order: skip rather than fault
+    for (bool more = true; more;) {
+        // with a processing order one template per wave in runs per XCD (run_item), else one atomic per wave on a
+        // uniform address, as in k_stat_wave
+        int64_t i;
+        if (a.order) {
+            int unit;
+            const int64_t item = run_item(a.n, unit);
+            if (item >= a.n) break;
+            i = (int64_t)__builtin_amdgcn_readfirstlane(a.order[item]);
+            if (i < 0 || i >= a.n) break;  // malformed processing order: skip rather than fault
+            more = false;
+        } else {
+            const uint32_t mine = atomicAdd(a.counter, lane == 0 ? 1u : 0u);
+            i = (int64_t)__builtin_amdgcn_readfirstlane(mine);
+            if (i >= a.n) break;
+        }
         const int ns = a.nseg[i];
         const int64_t off = a.seg_offset[i];
         SegAccRi<NR> acc;
@@ -262,6 +274,7 @@ hipError_t launch_statistic_interleaved(const StatLaunch &L, hipStream_t st) {
     const int bw = L.block_waves;
     int64_t groups = (L.n + bw - 1) / bw;
     if (groups > (int64_t)L.n_groups) groups = L.n_groups;
+    if (L.order) groups = run_groups(L.n, bw, 1);
     const int g = (int)groups;
     if (L.pix_dtype == 4) return dispatch_ri<int16_t>(L, a, g, bw, st);
     return dispatch_ri<float>(L, a, g, bw, st);

@@ -179,3 +179,24 @@ def test_vjp_units_equal_whole_templates(C, layout, dtype, precision):
     a, b = out[0][:5003], out[1]
     assert torch.isfinite(b).all()
     assert float(((a - b).abs() / a.abs().amax(dim=0)).max()) < 1e-9
+
+
+@pytest.mark.parametrize("n, n_real, C", [(1, 2, 1), (515, 2, 2), (2049, 4, 1)])
+def test_interleaved_runs_equal_the_counter(n, n_real, C):
+    """Realisations cell by cell: runs of the processing order per XCD against the work counter, bit for bit."""
+    tfsc = lib()
+    g = ti.custom_grid(C, 64, 130, dt=5.0, modulated=False, gapped=False, cfg_id=11)
+    grid = gridspec(g)
+    stores = []
+    for r in range(n_real):
+        rng = np.random.default_rng(r)
+        z = rng.standard_normal((C, 33, 130)) + 1j * rng.standard_normal((C, 33, 130))
+        stores.append(tfsc.PixelStore.from_complex(dev(z), dev(np.ones(33)), dev(np.ones(130)), "f32", "layer_ci"))
+    ri = tfsc.interleave_stores(grid, stores)
+    bank = _bank(tfsc, n, 23)
+    seg = tfsc.segment_layout(grid, bank)
+    note(f"interleaved runs against the counter: n={n} realisations={n_real} C={C}")
+    a = tfsc.bank_statistic_interleaved(grid, ri, n_real, bank, seg, order=tfsc.processing_order(grid, bank), want_active=True)
+    b = tfsc.bank_statistic_interleaved(grid, ri, n_real, bank, seg, want_active=True)
+    for k in ("stat", "seg_terms", "flags", "n_active"):
+        assert torch.equal(getattr(a, k), getattr(b, k)), k
