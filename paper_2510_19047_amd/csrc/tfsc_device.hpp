@@ -292,6 +292,7 @@ template <class R>
 __device__ __forceinline__ R sinc_rev2pi(R y) {
 #pragma clang fp contract(fast)
     const R q = sin_rev(y) * rcp(y);
+    if constexpr (sizeof(R) == 4) return y < 1.6e-5f ? (float)kTwoPi : q;  // the series, rounded: y^2 adds nothing
     const R ser = (R)kTwoPi - y * y * (R)(kTwoPi * kTwoPi * kTwoPi / 6.0);
     return y < (R)1.6e-5 ? ser : q;
 }
@@ -698,7 +699,7 @@ __device__ __forceinline__ int tranche_setup(TrancheSpec<R> &ts, double Phi, dou
     ts.beta = (R)beta;
     {
         // rational-branch bin ranges of the two edges, decided in FP64 (|v| <= 6 is rational)
-        const double r6 = sqrt(18.0 * beta);  // 6 / s with s = sqrt(2 / beta)
+        const double r6 = sqrt_pos(18.0 * beta);  // 6 / s with s = sqrt(2 / beta)
         ts.j0lo = (int)ceil(x - r6);
         ts.j0hi = (int)floor(x + r6);
         ts.j1lo = (int)ceil((x + beta) - r6);

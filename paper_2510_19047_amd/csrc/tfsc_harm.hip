@@ -153,14 +153,14 @@ __global__ __launch_bounds__(256, 2) void k_stat_wave_harm(StatArgs a, HarmArgs 
                 const double s = 0.5 * (double)hm.h[q];
                 TrancheSpec<R> ts;
                 int kc = 0;
-                int nlo = INT_MIN, hi = INT_MIN;
+                int jlo = 0, jhi = 0;
                 if (work) {
                     kc = tranche_setup(ts, s * Phi, s * f, s * fdot, a.dT, f);
-                    nlo = -ts.j0lo;
-                    hi = ts.j1hi;
+                    jlo = ts.j0lo;
+                    jhi = ts.j1hi;
                 }
-                wave_max2_i32(nlo, hi);
-                const int jA = -nlo, jB = hi;
+                int jA, jB;
+                wave_band(work, jlo, jhi, jA, jB);
                 const bool low = __ballot(work && kc < kHalfBins) != 0;
                 const uint32_t kbits = (uint32_t)kc & 0xffffu;
                 if (q == 0) kpack0 = kbits;

@@ -534,15 +534,14 @@ __global__ __launch_bounds__(256, 4) void k_stat_wave_multi(StatArgs a) {
             n_act += __popcll(__ballot(work));
             TrancheSpec<R> ts;
             int kc = 0;
-            int nlo = INT_MIN, hi = INT_MIN;
+            int jlo = 0, jhi = 0;
             if (work) {
                 kc = tranche_setup(ts, Phi, f, fdot, a.dT);
-                nlo = -ts.j0lo;
-                hi = ts.j1hi;
+                jlo = ts.j0lo;
+                jhi = ts.j1hi;
             }
-            wave_max2_i32(nlo, hi);
-            const int jA = -nlo;
-            const int jB = hi;
+            int jA, jB;
+            wave_band(work, jlo, jhi, jA, jB);
             const bool low = __ballot(work && kc < kHalfBins) != 0;
             R nn = 0;
             if (work) {

@@ -248,25 +248,28 @@ __device__ __forceinline__ float dpp_max_f32(float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
-template <int CTRL, int RM, int BM>
-__device__ __forceinline__ void dpp_max_step2(int &a, int &b) {
-    const int ta = __builtin_amdgcn_update_dpp(INT_MIN, a, CTRL, RM, BM, false);
-    const int tb = __builtin_amdgcn_update_dpp(INT_MIN, b, CTRL, RM, BM, false);
+template <int CTRL>
+__device__ __forceinline__ void dpp_max_step2(uint32_t &a, uint32_t &b) {
+    const uint32_t ta = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a, CTRL, 0xf, 0xf, true);
+    const uint32_t tb = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
     a = max(a, ta);
     b = max(b, tb);
 }
 
-// Wave-wide maxima of two ints (lane 63 holds both after the row shifts and broadcasts),
-// interleaved so the two DPP moves of each step fill each other's hazard slots.
-__device__ __forceinline__ void wave_max2_i32(int &a, int &b) {
-    dpp_max_step2<0x111, 0xf, 0xf>(a, b);
-    dpp_max_step2<0x112, 0xf, 0xf>(a, b);
-    dpp_max_step2<0x114, 0xf, 0xe>(a, b);
-    dpp_max_step2<0x118, 0xf, 0xc>(a, b);
-    dpp_max_step2<0x142, 0xa, 0xf>(a, b);
-    dpp_max_step2<0x143, 0xc, 0xf>(a, b);
-    a = __builtin_amdgcn_readlane(a, 63);
-    b = __builtin_amdgcn_readlane(b, 63);
+// The wave's band [jA, jB]: the least jlo and the greatest jhi of its working lanes (|jlo|, |jhi| < kBandBias: the
+// compactness rule keeps both within 25; empty if no lane works).  Biased to positive numbers the maxima have the
+// identity 0, which a DPP source outside the row reads, so each step is one DPP instruction (as in wave_sum3).
+constexpr int kBandBias = 1 << 20;
+__device__ __forceinline__ void wave_band(bool work, int jlo, int jhi, int &jA, int &jB) {
+    uint32_t a = work ? (uint32_t)(kBandBias - jlo) : 0u, b = work ? (uint32_t)(kBandBias + jhi) : 0u;
+    dpp_max_step2<0x111>(a, b);
+    dpp_max_step2<0x112>(a, b);
+    dpp_max_step2<0x114>(a, b);
+    dpp_max_step2<0x118>(a, b);
+    dpp_max_step2<0x142>(a, b);
+    dpp_max_step2<0x143>(a, b);
+    jA = kBandBias - __builtin_amdgcn_readlane((int)a, 63);
+    jB = __builtin_amdgcn_readlane((int)b, 63) - kBandBias;
 }
 
 template <class R>
@@ -847,20 +850,16 @@ __device__ __forceinline__ void stat_wave_body(const StatArgs &a) {
             n_act += __popcll(__ballot(work));
             TrancheSpec<R> ts;
             int kc = 0;
-            int nlo = INT_MIN, hi = INT_MIN;  // -(first) and last bin that is not asymptotic-only
+            int jlo = 0, jhi = 0;  // first and last bin that is not asymptotic-only
             if (work) {
                 kc = tranche_setup(ts, Phi, f, fdot, a.dT);
-                nlo = -ts.j0lo;
-                hi = ts.j1hi;
+                jlo = ts.j0lo;
+                jhi = ts.j1hi;
             }
             // The wave takes the general form on the union [jA, jB] of the lanes' such bins (on all bins in the
             // accurate Fresnel mode, which has no asymptotic-only form).
             int jA = -kHalfBins, jB = kHalfBins;
-            if constexpr (FR == kFresnelPaper) {
-                wave_max2_i32(nlo, hi);
-                jA = -nlo;
-                jB = hi;
-            }
+            if constexpr (FR == kFresnelPaper) wave_band(work, jlo, jhi, jA, jB);
             R zr = 0, zi = 0, nn = 0;
             const bool low = __ballot(work && kc < kHalfBins) != 0;
             cx<R> P[C];
