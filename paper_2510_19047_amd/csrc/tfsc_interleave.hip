@@ -108,7 +108,7 @@ __global__ __launch_bounds__(256, 3) void k_stat_wave_ri(StatArgs a) {
         if (a.order) {
             int unit;
             const int64_t item = run_item(a.n, unit);
-            if (item >= a.n) break;
+            if (item >= a.n || unit > 0) break;
             i = (int64_t)__builtin_amdgcn_readfirstlane(a.order[item]);
             if (i < 0 || i >= a.n) break;  // malformed processing order: skip rather than fault
             more = false;

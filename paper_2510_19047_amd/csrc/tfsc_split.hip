@@ -9,8 +9,8 @@
 // sums (SplitUnit) and the later ones each chunk's (head), and k_stat_finish adds them in the order of k_stat_wave: the
 // results are the same bits.
 //
-// Bound: latency for few templates (20 of 96 chunks: 33 us with its three launches, whole templates 533), vector-ALU
-// issue from a few thousand on.  The rule and its figures: split_shape.
+// Bound: latency for few templates (20 of 96 chunks: 36 us a call with its three launches, whole templates 547), vector-
+// ALU issue from a few thousand on.  The rule and its figures: split_shape.
 #include "tfsc_stat_common.hpp"
 
 namespace tfsc {
@@ -18,6 +18,13 @@ namespace tfsc {
 template <int C, class R, class PixT, int LAYOUT, bool RHO>
 __global__ __launch_bounds__(256, 4) void k_stat_split(StatArgs a) {
     stat_wave_body<C, R, PixT, LAYOUT, RHO, kFresnelPaper, false, kUnits>(a);
+}
+
+// One chunk per wave: two waves per SIMD, whose registers hold all the pixels of a chunk, so that they cost one latency
+// instead of seven (the rows lie a page or more apart).
+template <int C, class R, class PixT, int LAYOUT, bool RHO>
+__global__ __launch_bounds__(256, 2) void k_stat_chunk(StatArgs a) {
+    stat_wave_body<C, R, PixT, LAYOUT, RHO, kFresnelPaper, false, kChunk>(a);
 }
 
 // Whole templates of a bank with a processing order.
@@ -38,18 +45,23 @@ __global__ __launch_bounds__(256) void k_stat_finish(StatArgs a) {
     const int64_t off = a.seg_offset[i];
     const bool valid = a.split.rec[i * kRecDoubles + kRecValid] != 0.0;
     const SplitUnit *un = a.split.unit + i * units;
-    // the unit in which the track ends (units: in none) and its last chunk; units after it do not count
-    int ue = units, n_act = 0, any = 0;
+    // the unit in which the track ends (units: in none), its flag and tranche; units after it do not count
+    int ue = units, code = 0, m_end = valid ? a.Nt : 0, n_act = 0, any = 0;
     for (int u0 = 0; valid && u0 < units && ue == units; u0 += 64) {
-        const int u = u0 + lane;
-        const uint64_t ends = __ballot(u < units && un[u].code != 0);
-        if (ends) ue = u0 + __ffsll((unsigned long long)ends) - 1;
+        const int u = u0 + lane, ul = min(u, units - 1);
+        const int uc = un[ul].code, um = un[ul].m_end, ua = un[ul].n_act, us = un[ul].any;
+        const uint64_t ends = __ballot(u < units && uc != 0);
+        if (ends) {
+            const int l = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)ends) - 1);
+            ue = u0 + l;
+            code = __builtin_amdgcn_readlane(uc, l);
+            m_end = __builtin_amdgcn_readlane(um, l);
+        }
         const bool counts = u < units && u <= ue;
-        n_act += counts ? un[u].n_act : 0;
-        any |= counts ? un[u].any : 0;
+        n_act += counts ? ua : 0;
+        any |= counts ? us : 0;
     }
     for (int o = 32; o > 0; o >>= 1) n_act += __shfl_xor(n_act, o, 64);
-    const int m_end = !valid ? 0 : (ue < units ? un[ue].m_end : a.Nt);
     const int last_chunk = m_end >> 6;  // a track that ends at a chunk's first tranche adds nothing there
     double total = 0.0;
     for (int s0 = 0; s0 < ns; s0 += 64) {
@@ -68,11 +80,21 @@ __global__ __launch_bounds__(256) void k_stat_finish(StatArgs a) {
                     zi = un[ua].zi;
                     N = un[ua].N;
                     const int c1 = min((hi - 1) >> 6, m_end & 63 ? last_chunk : last_chunk - 1);
-                    for (int c = (ua + 1) * a.split.chunks; c <= c1; ++c) {
-                        const R *h = reinterpret_cast<const R *>(a.split.head) + (i * a.split.n_chunks + c) * 3;
-                        zr += (double)h[0];
-                        zi += (double)h[1];
-                        N += (double)h[2];
+                    const R *head = reinterpret_cast<const R *>(a.split.head) + i * a.split.n_chunks * 3;
+                    // eight chunks' loads are in flight together; the sums keep their order
+                    for (int c = (ua + 1) * a.split.chunks; c <= c1; c += 8) {
+                        R h[8][3];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q)
+#pragma unroll
+                            for (int e = 0; e < 3; ++e) h[q][e] = head[3 * min(c + q, c1) + e];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q)
+                            if (c + q <= c1) {
+                                zr += (double)h[q][0];
+                                zi += (double)h[q][1];
+                                N += (double)h[q][2];
+                            }
                     }
                 }
                 v = N > 0.0 ? 2.0 * (zr * zr + zi * zi) / N : 0.0;
@@ -90,7 +112,7 @@ __global__ __launch_bounds__(256) void k_stat_finish(StatArgs a) {
     }
     const bool some = __ballot(any != 0) != 0;
     if (lane == 0) {
-        int flag = valid ? (ue < units ? un[ue].code : 0) : kFlagInvalid;
+        int flag = valid ? code : kFlagInvalid;
         if (valid && m_end == 0) flag |= kFlagEmpty;
         if (valid && !some && m_end > 0) flag |= kFlagAllExcluded;
         a.stat[i] = total;
@@ -105,8 +127,13 @@ static hipError_t launch_split_l(const StatArgs &a, int block_waves, hipStream_t
     const size_t shmem = sizeof(R) * KP + (PixTraits<PixT>::scaled ? sizeof(float) * C * KP : 0);
     const dim3 block(64 * block_waves);
     if (a.split.units) {
-        hipLaunchKernelGGL((k_stat_split<C, R, PixT, LAYOUT, RHO>), dim3(run_groups(a.n, block_waves, a.split.units)), block,
-                           shmem, st, a);
+        const dim3 grid(run_groups(a.n, block_waves, a.split.units));
+        // Up to 8192 chunks (two rounds of four waves per SIMD) latency counts: 257 templates of 20 chunks 28.7 us a call
+        // against 30.5 with k_stat_split, 20 of 96 in FP64 45 against 61; from 10,000 chunks on both take the same.
+        if (a.split.chunks == 1 && a.n * a.split.units <= 8192)
+            hipLaunchKernelGGL((k_stat_chunk<C, R, PixT, LAYOUT, RHO>), grid, block, shmem, st, a);
+        else
+            hipLaunchKernelGGL((k_stat_split<C, R, PixT, LAYOUT, RHO>), grid, block, shmem, st, a);
         hipLaunchKernelGGL(k_stat_finish<R>, dim3((unsigned)((a.n + 3) / 4)), dim3(256), 0, st, a);
     } else {
         hipLaunchKernelGGL((k_stat_runs<C, R, PixT, LAYOUT, RHO>), dim3(run_groups(a.n, block_waves, 1)), block, shmem, st, a);

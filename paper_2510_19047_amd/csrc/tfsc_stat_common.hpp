@@ -502,14 +502,15 @@ __device__ __forceinline__ void bin_accumulate(const TrancheSpec<R> &ts, int j, 
 // read lies in the store; a lane with kc < 10 would need a row below 0, and a wave holding
 // such a lane takes wave_tranche_bins_low instead.  The exact Fresnel form is used only for
 // the bins [jA, jB] where some lane of the wave may need it (a wave-uniform choice).
-template <int C, class R, class PixT, int LAYOUT, bool RHO, int FR = kFresnelPaper>
+// G: bins whose loads are in flight together (3, or as many as the registers hold where latency counts).
+template <int C, class R, class PixT, int LAYOUT, bool RHO, int FR = kFresnelPaper, int G = 3>
 __device__ __forceinline__ void wave_tranche_bins(const TrancheSpec<R> &ts, int kc, int m, int Nt, int K,
                                                   __amdgpu_buffer_rsrc_t rsrc, __amdgpu_buffer_rsrc_t rho_rsrc,
                                                   const R *__restrict__ u_pad, const float *__restrict__ sc_pad,
                                                   int jA, int jB, cx<R> (&P)[C], R &Q) {
     constexpr uint32_t B = sizeof(PixT) == 8 ? 16u : (sizeof(PixT) == 4 ? 8u : 4u);
     constexpr uint32_t BP = LAYOUT == 2 ? (uint32_t)C * B : B;  // bytes per (bin, tranche) cell
-    constexpr int NB = 2 * kHalfBins + 1, G = 3;
+    constexpr int NB = 2 * kHalfBins + 1;
     static_assert(NB % G == 0, "bin groups must tile the window");
     const uint32_t voff = (uint32_t)((kc - kHalfBins) * Nt + m) * BP;
     const uint32_t row = (uint32_t)Nt * BP, chan = (uint32_t)K * row;
@@ -619,20 +620,34 @@ __device__ __forceinline__ void wave_uniform(Sky<R> &S) {
 // ------------------------------------------------------------------ work in runs per XCD
 // The place in the processing order that a wave of a grid of run_groups blocks takes (n or more: none), and its unit.
 // All templates of a unit come before the next unit.  Within it XCD x (blocks go round the 8 XCDs) takes every eighth run
-// of kSplitRun templates in processing order: the waves that run together on an XCD read neighbouring rows of the same
-// time, which its L2 then holds, and long and short tracks are spread over the XCDs.
-__device__ __forceinline__ int64_t run_item(int64_t n, int &unit) {
-    const uint32_t w = blockDim.x >> 6, run = kSplitRun / w;  // blocks per run (w is 1 to 4)
-    const uint32_t len = 8 * run * w, per = (uint32_t)((n + len - 1) / len) * run;  // blocks per XCD and unit
+// of at most kSplitRun templates in processing order: the waves that run together on an XCD read neighbouring rows of the
+// same time, which its L2 then holds, and long and short tracks are spread over the XCDs.  The runs are as many as 8 XCDs
+// share evenly.  Fewer than one full run per XCD (n < 8 kSplitRun) are dealt out to all XCDs in order instead: in runs, 20
+// templates of 96 chunks would sit on one XCD (91 us against 16).
+__host__ __device__ inline uint32_t run_blocks(uint32_t n, uint32_t w, uint32_t &rounds) {  // w: templates per block
+    rounds = (n + 8 * kSplitRun - 1) / (8 * kSplitRun);
+    return (n + 8 * rounds * w - 1) / (8 * rounds * w);
+}
+
+__device__ __forceinline__ int64_t run_item(int64_t n64, int &unit) {
+    const uint32_t n = (uint32_t)n64, w = blockDim.x >> 6, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (n < 8 * kSplitRun) {
+        const uint32_t e = blockIdx.x * w + wave;
+        unit = (int)(e / n);
+        return e - (uint32_t)unit * n;
+    }
+    uint32_t rounds;
+    const uint32_t run = run_blocks(n, w, rounds), per = rounds * run;  // blocks per run; per XCD and unit
     const uint32_t j = (blockIdx.x >> 3) % per;
     unit = (int)((blockIdx.x >> 3) / per);
-    return ((int64_t)(j / run) * 8 + (blockIdx.x & 7)) * (run * w) + (j % run) * w +
-           __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    return ((int64_t)(j / run) * 8 + (blockIdx.x & 7)) * (run * w) + (j % run) * w + wave;
 }
 
 inline unsigned run_groups(int64_t n, int block_waves, int units) {
-    const int run = kSplitRun / block_waves, len = 8 * run * block_waves;
-    return (unsigned)((n + len - 1) / len * 8 * run * units);
+    if (n < 8 * kSplitRun) return (unsigned)((n * units + block_waves - 1) / block_waves);
+    uint32_t rounds;
+    const uint32_t run = run_blocks((uint32_t)n, (uint32_t)block_waves, rounds);
+    return 8 * rounds * run * (unsigned)units;
 }
 
 // ------------------------------------------------------------------ template records
@@ -741,15 +756,17 @@ __device__ __forceinline__ void stat_thread_body(const StatArgs &a) {
 
 // The body of the wave-per-template kernels (k_stat_wave; the accurate-Fresnel variant, which takes the
 // general form on all 21 bins; the unequal-arm variant, LK) and of its forms with one item per wave: kRuns, whole
-// templates in runs per XCD (k_stat_runs), and kUnits, some consecutive 64-tranche chunks of a template (k_stat_split).
-// The arithmetic of a chunk is the same in all.
-enum : int { kCounter = 0, kRuns = 1, kUnits = 2 };
+// templates in runs per XCD (k_stat_runs), kUnits, some consecutive 64-tranche chunks of a template (k_stat_split), and
+// kChunk, one chunk (k_stat_chunk: all its loads in flight together, no track ahead).  The arithmetic of a chunk is the
+// same in all.
+enum : int { kCounter = 0, kRuns = 1, kUnits = 2, kChunk = 3 };
 
 template <int C, class R, class PixT, int LAYOUT, bool RHO, int FR, bool LK = false, int FETCH = kCounter>
 __device__ __forceinline__ void stat_wave_body(const StatArgs &a) {
     // Zero-padded template weights u_pad[k + 10] = u_k for 1 <= k <= M/2 - 1 (else 0), and
     // the 16-bit layer scales, staged in LDS once per block.
-    constexpr bool SPLIT = FETCH == kUnits, ONE = FETCH != kCounter;
+    constexpr bool SPLIT = FETCH == kUnits || FETCH == kChunk, ONE = FETCH != kCounter;
+    constexpr int G = FETCH != kChunk ? 3 : (C * sizeof(PixT) <= 12 ? 21 : 7);  // bins loaded together
     extern __shared__ unsigned char smem_raw[];
     const int KP = a.K + 2 * kHalfBins;
     R *u_pad = reinterpret_cast<R *>(smem_raw);
@@ -776,7 +793,7 @@ __device__ __forceinline__ void stat_wave_body(const StatArgs &a) {
         int unit = 0;
         if constexpr (ONE) {
             item = run_item(a.n, unit);
-            if (item >= a.n) break;
+            if (item >= a.n || unit >= (SPLIT ? a.split.units : 1)) break;
         } else {
             // Work fetch in converged code: every lane joins one atomic on a uniform address
             // (lane 0 adds 1, the others 0), which the compiler turns into a single atomic per
@@ -869,14 +886,14 @@ __device__ __forceinline__ void stat_wave_body(const StatArgs &a) {
                     wave_tranche_bins_low<C, R, PixT, LAYOUT, RHO, FR>(ts, kc, m, a.Nt, a.K, rsrc, rho_rsrc, u_pad, sc_pad,
                                                                    jA, jB, P, Q);
                 else
-                    wave_tranche_bins<C, R, PixT, LAYOUT, RHO, FR>(ts, kc, m, a.Nt, a.K, rsrc, rho_rsrc, u_pad, sc_pad,
-                                                               jA, jB, P, Q);
+                    wave_tranche_bins<C, R, PixT, LAYOUT, RHO, FR, G>(ts, kc, m, a.Nt, a.K, rsrc, rho_rsrc, u_pad, sc_pad,
+                                                                  jA, jB, P, Q);
             }
             // this chunk's response and the next chunk's track, for every lane (values of lanes without work
             // are not used; the geometry row is clamped into the table)
             cx<R> Tc[C];
             tranche_transfer<C, R, LK>(S, gv, inr ? m : a.Nt - 1, f, Tc);
-            {
+            if constexpr (FETCH != kChunk) {
                 const int mn = m + 64;
                 int cn = track_step_lanes(T, (double)(mn < a.Nt ? mn : a.Nt - 1) * a.dT, a.dT, a.df, a.fnyq, Phi, f,
                                           fdot);

@@ -698,7 +698,7 @@ __global__ __launch_bounds__(256, sizeof(R) == 4 ? 2 : 1) void k_vjp_wave(VjpArg
     const int lane = threadIdx.x & 63;
     int unit;
     const int64_t i = run_item(a.n, unit);
-    if (i >= a.n) return;
+    if (i >= a.n || unit >= a.units) return;
     {
         double gr[5] = {0, 0, 0, 0, 0};
         const double mci = a.mc[i];

@@ -124,6 +124,13 @@ def test_split_templates_equal_whole_ones(precision, nseg):
             b = tfsc.bank_statistic_noalloc(g, store, bank, seg, precision=precision, want_zn=True, want_active=True,
                                             order=o)
             _all_equal(a, b)
+        if n == 5000:  # fewer than a run per XCD: the first templates of this bank by themselves, their terms in the same places
+            few = tfsc.BankTensors(*(getattr(bank, k)[:300].contiguous() for k in tfsc.BankTensors.FIELDS))
+            fs = tfsc.segment_layout(g, few, nseg)
+            c = tfsc.bank_statistic(g, store, few, fs, precision=precision, want_zn=True, want_active=True)
+            for k in ("stat", "flags", "n_active"):
+                assert torch.equal(getattr(c, k), getattr(a, k)[:300]), k
+            assert torch.equal(c.seg_terms, a.seg_terms[: fs.total]) and torch.equal(c.seg_zn, a.seg_zn[: fs.total])
 
 
 @pytest.mark.parametrize("block_waves", [1, 3, 4])
