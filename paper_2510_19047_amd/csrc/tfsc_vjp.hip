@@ -112,9 +112,13 @@ template <int N, class R>
 __device__ __forceinline__ Dn<N, R> operator-(nd_t<R> s, Dn<N, R> a) {
     return (-a) + s;
 }
+// 1/x.  The FP64 operands here are normal and far from the range limits (see rcp_rn: the division's bits for 7 of its 11
+// instructions).
+__device__ __forceinline__ double vrcp(double x) { return rcp_rn(x); }
+__device__ __forceinline__ float vrcp(float x) { return rcp(x); }
 template <int N, class R>
 __device__ __forceinline__ Dn<N, R> drcp(Dn<N, R> a) {
-    const R r = rcp(a.v), r2 = -r * r;
+    const R r = vrcp(a.v), r2 = -r * r;
     Dn<N, R> o;
     o.v = r;
 #pragma unroll
@@ -123,7 +127,7 @@ __device__ __forceinline__ Dn<N, R> drcp(Dn<N, R> a) {
 }
 __device__ __forceinline__ double vsqrt(double x) { return sqrt(x); }
 __device__ __forceinline__ float vsqrt(float x) { return sqrtf(x); }
-__device__ __forceinline__ double half_rcp(double s) { return 0.5 / s; }
+__device__ __forceinline__ double half_rcp(double s) { return 0.5 * rcp_rn(s); }
 __device__ __forceinline__ float half_rcp(float s) { return 0.5f * rcp(s); }
 template <int N, class R>
 __device__ __forceinline__ Dn<N, R> dsqrt(Dn<N, R> a) {
@@ -162,10 +166,12 @@ __device__ __forceinline__ void sinc_d(double x, double &v, double &dv) {
         v = 1.0 - x * x * (1.0 / 6.0);
         dv = -x * (1.0 / 3.0);
     } else {
+        // in half turns: no reduction of large arguments (pi f L (1 -+ k.n) is below a few turns)
         double s, c;
-        sincos(x, &s, &c);
-        v = s / x;
-        dv = (c - v) / x;
+        sincospi(x * (1.0 / kPi), &s, &c);
+        const double ir = rcp_rn(x);
+        v = s * ir;
+        dv = (c - v) * ir;
     }
 }
 __device__ __forceinline__ void sinc_d(float x, float &v, float &dv) {
@@ -272,6 +278,7 @@ struct TrackDual {
     double dPhi[2], df[2], dfdot[2];
 };
 
+template <class R>
 __device__ inline TrackDual track_dual(const Track &T, const TrackTan &G, double t, double f, double s) {
     const double tau = T.tc - t;
     const double itau = rcp_rn(tau);
@@ -292,7 +299,13 @@ __device__ inline TrackDual track_dual(const Track &T, const TrackTan &G, double
         const double dth = -0.125 * th * (G.dtc[p] * itau - mu);
         D.df[p] = dfdth * dth - f * mu;
         const double d_dfdth = ((2.0 * th * dPf + th2 * ddPf) * T.rc8) * dth - dfdth * mu;
-        const double d_dthdt = dthdt * (9.0 * dth / th - mu);
+        // FP32 form: the quotient, whose rounding its results carry; FP64 form: s = 1/theta
+        double dlnth;
+        if constexpr (sizeof(R) == 4)
+            dlnth = 9.0 * dth / th;
+        else
+            dlnth = 9.0 * dth * s;
+        const double d_dthdt = dthdt * (dlnth - mu);
         D.dfdot[p] = d_dfdth * dthdt + dfdth * d_dthdt;
         D.dPhi[p] = dPhidth * dth;
     }
@@ -432,9 +445,10 @@ __device__ inline int spec_dual(SpecD<R> &S, double Phi, double f, double fdot, 
     S.x = dconst<2, R>((R)x);
     S.beta = dconst<2, R>((R)beta);
     Dn<2, R> A, Fd = dconst<2, R>((R)fdot);
-    if constexpr (sizeof(R) == 8)
-        A.v = pow(f, 2.0 / 3.0);
-    else
+    if constexpr (sizeof(R) == 8) {
+        const double c = cbrt(f);
+        A.v = c * c;
+    } else
         A.v = __builtin_amdgcn_exp2f(__builtin_amdgcn_logf((float)f) * (2.0f / 3.0f));
     const R dlnA = (R)(2.0 / 3.0) * (A.v / (R)f);
     const double rev0 = phase_to_rev(Phi);
@@ -584,7 +598,7 @@ struct VjpMoments {
 
     __device__ __forceinline__ void add(R xj, R beta, R u, const cx<R> (&D)[C]) {
         const R xj1 = xj + beta;
-        const R t = rcp(xj * xj1), a = xj1 * t, b = xj * t;
+        const R t = vrcp(xj * xj1), a = xj1 * t, b = xj * t;
         const R f1 = u * b, f0 = f1 * a, f2 = f1 * b, f3 = f0 * a, f4 = f0 * b;
         G00 += f0 * f0;
         G01 += f0 * f1;
@@ -680,7 +694,8 @@ struct VjpArgs {
 //
 // Bound: FP64, latency of dependent FP64 chains at one wave per SIMD; FP32, vector-ALU issue at two.  Two-year grid, A+E:
 // 320 templates FP64 2282 us with a wave per template and the tangents carried through every bin, 1058 in units with the
-// moments, 913 with each lane's own band instead of the wave's; 65,536 templates FP32 40 -> 33.7 ms from units in runs
+// moments, 913 with each lane's own band instead of the wave's, 590 with the units dealt out to all XCDs, 527 with sincospi
+// and reciprocals for sincos, pow and divisions; 65,536 templates FP32 40 -> 33.7 ms from units in runs
 // per XCD, a pixel's address in one multiply-add for every layout, and the next bin's loads ahead.
 template <int C, class PixT, class R>
 __global__ __launch_bounds__(256, sizeof(R) == 4 ? 2 : 1) void k_vjp_wave(VjpArgs a) {
@@ -783,7 +798,7 @@ __global__ __launch_bounds__(256, sizeof(R) == 4 ? 2 : 1) void k_vjp_wave(VjpArg
                         const int m_ref = (int)(((int64_t)sn * a.Nt + ns - 1) / ns);
                         double dref[2];
                         dphi_at(T, TT, (double)m_ref * a.dT, dref);
-                        const TrackDual TD = track_dual(T, TT, (double)m * a.dT, f, s_th);
+                        const TrackDual TD = track_dual<R>(T, TT, (double)m * a.dT, f, s_th);
                         dfr[0] = (R)TD.df[0];
                         dfr[1] = (R)TD.df[1];
                         SpecD<R> sp;
