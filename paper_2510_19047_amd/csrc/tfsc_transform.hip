@@ -49,9 +49,10 @@ __device__ __forceinline__ cx<float> twiddle<float>(double frac) {
 // 100.8 MB store).
 //
 // Bound: latency, at three waves per SIMD (the registers and 53 KB of LDS allow no more); the vector ALU is busy for
-// half the time, the LDS for a third.  Two years of A+E, FP32 (100.7 MB in, 100.8 MB out): 97 us, 2.1 TB/s, against
+// half the time, the LDS for a third.  Two years of A+E, FP32 (100.7 MB in, 100.8 MB out): 87 us, 2.3 TB/s, against
 // 520 us with one exchange per stage, a branch (and a wait) around every load and 8-byte stores.  Holding the runs of
-// four tranches, the window or the whitening factors in registers across the transforms spilled and took 139-168 us.
+// four tranches or the window in registers across the transforms spilled and took 139-168 us; forming the whitening
+// factors (a division and a square root per bin and tranche, 40% of the instructions) for each channel anew, 97 us.
 // -i w: the twiddle a quarter turn on.  For a twiddle below exp(-i pi / 4) it has the table's bits; from there on the
 // table's own entry is read (its sine and cosine of pi / 4 differ in the last place).
 template <class R>
@@ -153,7 +154,11 @@ __global__ __launch_bounds__(M == 4096 ? 512 : 256, CC == 3 ? 2 : 3) void k_tran
         const int m0 = ((tile * NF + fl) * NG + grp) * TB;
         // held[it][i][tr]: bin k = t + i M/8 of tranche m + tr; DC and Nyquist are real, so bin 0 holds (DC, Nyquist)
         cx<OutT> held[NIT][4][2] = {};
-#pragma unroll 1
+        R sc[4][2], scn[2];
+        // a cell's channels one after the other without a loop, so that the pair's whitening factors and the values
+        // held live only as long as they must; of one channel the loop stays (unrolled it would spill)
+        constexpr int kUnroll = CC == 1 ? 1 : NIT;
+#pragma unroll kUnroll
         for (int it = 0; it < NIT; ++it) {
             const int c = c0 + it % CC, m = m0 + 2 * (it / CC);
             // the thread's index anew for each transform: the addresses, window and PSD values that depend on it are then
@@ -235,12 +240,11 @@ __global__ __launch_bounds__(M == 4096 ? 512 : 256, CC == 3 ? 2 : 3) void k_tran
                 }
                 __syncthreads();
             }
-            // the whitening factors, where the transform's registers are free (held over a cell's channels they would spill)
+            // the whitening factors of the pair, where the transform's registers are free
             const int ma = min(m, Nt - 1), mb = min(m + 1, Nt - 1);
             const double mua = L.psd_tf ? 1.0 : L.mu[ma], mub = L.psd_tf ? 1.0 : L.mu[mb];
             const bool ka = L.keep[ma] != 0, kb = L.keep[mb] != 0;
-            R sc[4][2], scn[2] = {};
-            {
+            if (it % CC == 0) {
                 double sa[4], sb[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
