@@ -107,15 +107,18 @@ class Background:
     def __init__(self, tile: np.ndarray, n_tiles: int, device="cuda"):
         self.n_tiles = int(n_tiles)
         self.tile = torch.from_numpy(np.ascontiguousarray(tile, dtype=np.int32)).to(device)
-        self._out = None
+        self._both = None  # maxima and indices side by side, so that one copy brings both to the host
         self.rows: list[np.ndarray] = []
         self.arg_rows: list[np.ndarray] = []
 
     def add(self, stat: torch.Tensor) -> np.ndarray:
-        self._out = tile_max(stat, self.tile, self.n_tiles, out=self._out)
-        row = self._out[0].cpu().numpy().copy()
+        if self._both is None:
+            self._both = torch.empty((2, self.n_tiles), dtype=torch.float64, device=stat.device)
+        tile_max(stat, self.tile, self.n_tiles, out=(self._both[0], self._both[1].view(torch.int64)))
+        host = self._both.cpu().numpy()
+        row = host[0].copy()
         self.rows.append(row)
-        self.arg_rows.append(self._out[1].cpu().numpy().copy())
+        self.arg_rows.append(host[1].view(np.int64).copy())
         return row
 
     @property
