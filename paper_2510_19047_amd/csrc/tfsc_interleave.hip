@@ -102,10 +102,10 @@ __global__ __launch_bounds__(256, 3) void k_stat_wave_ri(StatArgs a) {
     const int lane = threadIdx.x & 63;
     const bool writer = lane == 0;
     for (bool more = true; more;) {
-        // with a processing order one template per wave in runs per XCD (run_item), else one atomic per wave on a
-        // uniform address, as in k_stat_wave
+        // with a processing order one template per wave in runs per XCD (run_item; up to kRunsMost of them), else one
+        // atomic per wave on a uniform address, as in k_stat_wave
         int64_t i;
-        if (a.order) {
+        if (a.order && a.n <= kRunsMost) {
             int unit;
             const int64_t item = run_item(a.n, unit);
             if (item >= a.n || unit > 0) break;
@@ -116,6 +116,10 @@ __global__ __launch_bounds__(256, 3) void k_stat_wave_ri(StatArgs a) {
             const uint32_t mine = atomicAdd(a.counter, lane == 0 ? 1u : 0u);
             i = (int64_t)__builtin_amdgcn_readfirstlane(mine);
             if (i >= a.n) break;
+            if (a.order) {
+                i = (int64_t)__builtin_amdgcn_readfirstlane(a.order[i]);
+                if (i < 0 || i >= a.n) continue;
+            }
         }
         const int ns = a.nseg[i];
         const int64_t off = a.seg_offset[i];
@@ -274,7 +278,7 @@ hipError_t launch_statistic_interleaved(const StatLaunch &L, hipStream_t st) {
     const int bw = L.block_waves;
     int64_t groups = (L.n + bw - 1) / bw;
     if (groups > (int64_t)L.n_groups) groups = L.n_groups;
-    if (L.order) groups = run_groups(L.n, bw, 1);
+    if (L.order && L.n <= kRunsMost) groups = run_groups(L.n, bw, 1);
     const int g = (int)groups;
     if (L.pix_dtype == 4) return dispatch_ri<int16_t>(L, a, g, bw, st);
     return dispatch_ri<float>(L, a, g, bw, st);

@@ -29,9 +29,12 @@ struct LayoutLaunch {
 };
 
 // Few templates: each template's chunks of 64 tranches are shared out in units of `chunks` of them, one unit per
-// wave (k_stat_split, k_vjp_split), and a finishing kernel joins the units.  units = 0: not split.
+// wave (k_stat_split, k_stat_chunk, k_vjp_units), and a finishing kernel joins the units.  units = 0: not split.
 constexpr int kSplitRun = 64;    // consecutive templates on one XCD (see run_item)
 constexpr int kRecDoubles = 32;  // doubles of a template record
+// Most whole templates in runs, one wave each: a grid holds fewer than 2^32 threads, 67 million waves.  Larger banks in a
+// processing order take the persistent grid and its work counter.
+constexpr int64_t kRunsMost = 1 << 25;
 struct SplitUnit {
     double zr, zi, N;  // sums of the segment that goes on into the next unit
     int code, m_end;   // flag and tranche of the track's end, if it ends in the unit (m_end: else the unit's end)

@@ -207,3 +207,30 @@ def test_interleaved_runs_equal_the_counter(n, n_real, C):
     b = tfsc.bank_statistic_interleaved(grid, ri, n_real, bank, seg, want_active=True)
     for k in ("stat", "seg_terms", "flags", "n_active"):
         assert torch.equal(getattr(a, k), getattr(b, k)), k
+
+
+@pytest.mark.parametrize("n", [1 << 25, (1 << 25) + 4096])
+def test_largest_bank_in_runs_and_the_first_on_the_counter(n):
+    """At the size where an ordered bank goes from one wave per template to the persistent grid (its grid would pass 2^32
+    threads at twice that): a bank of repeated templates gives the small bank's values, bit for bit."""
+    tfsc = lib()
+    g = ti.custom_grid(1, 64, 66, dt=5.0, modulated=False, gapped=False, cfg_id=11)
+    grid = gridspec(g)
+    rng = np.random.default_rng(4)
+    z = rng.standard_normal((1, 33, 66)) + 1j * rng.standard_normal((1, 33, 66))
+    store = tfsc.PixelStore.from_complex(dev(z), dev(np.ones(33)), dev(np.ones(66)), "f32", "layer_ci")
+    small = _bank(tfsc, 4096, 29)
+    seg = tfsc.segment_layout(grid, small, nseg_fixed=1)
+    want = tfsc.bank_statistic(grid, store, small, seg).stat
+    bank = tfsc.BankTensors(**{f: getattr(small, f).repeat(n // 4096) for f in small.FIELDS})
+    seg = tfsc.segment_layout(grid, bank, nseg_fixed=1)
+    order = tfsc.processing_order(grid, bank)
+    note(f"ordered bank of {n}")
+    got = tfsc.bank_statistic(grid, store, bank, seg, order=order)
+    assert torch.equal(got.stat.view(-1, 4096), want.expand(n // 4096, 4096))
+    del got
+    ri = tfsc.interleave_stores(grid, [store, store])
+    got = tfsc.bank_statistic_interleaved(grid, ri, 2, bank, seg, order=order)
+    want = tfsc.bank_statistic_interleaved(grid, ri, 2, small, tfsc.segment_layout(grid, small, nseg_fixed=1)).stat
+    for r in range(2):
+        assert torch.equal(got.stat[r].view(-1, 4096), want[r].expand(n // 4096, 4096)), r
