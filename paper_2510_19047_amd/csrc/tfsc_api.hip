@@ -275,6 +275,47 @@ tfsc::StatLaunch stat_launch(const tfsc_grid *grid, const tfsc_pixels *pix, cons
     return L;
 }
 
+// The statistic; from_counter: whole templates on the persistent grid, for the tuner.
+tfsc_status statistic_call(const tfsc_grid *grid, const tfsc_pixels *pix, const tfsc_bank *bank, const tfsc_segments *seg,
+                           const tfsc_options *opt, double *seg_terms, double *stat, double *seg_zn, int32_t *flags,
+                           int32_t *n_active, void *ws, size_t ws_bytes, void *stream, bool from_counter) {
+    tfsc_status s;
+    if ((s = check_grid(grid)) != TFSC_OK) return s;
+    if ((s = check_bank(bank)) != TFSC_OK) return s;
+    if ((s = check_pixels(pix, bank->n > 0)) != TFSC_OK) return s;
+    if (!seg || (bank->n > 0 && (!seg->nseg || !seg->seg_offset))) return TFSC_ERR_ARG;
+    Resolved r;
+    if ((s = resolve_options(opt, pix, r)) != TFSC_OK) return s;
+    if (bank->n > 0 && (!seg_terms || !stat || !flags)) return TFSC_ERR_ARG;
+    if (!ws || ws_bytes < stat_ws_bytes(grid, bank->n, bank->ln_mc != nullptr)) return TFSC_ERR_WORKSPACE;
+    if (r.schedule == TFSC_SCHED_WAVE && pixel_store_bytes(grid, pix) > 0xffffffffull) return TFSC_ERR_UNSUPPORTED;
+    if (pix->rho && r.schedule == TFSC_SCHED_WAVE && pix->dtype != TFSC_F64 && pix->dtype != TFSC_F32)
+        return TFSC_ERR_UNSUPPORTED;
+    if (r.fresnel == TFSC_FRESNEL_ACCURATE &&
+        (pix->rho || !((pix->dtype == TFSC_F64 && r.precision == TFSC_F64) ||
+                       (pix->dtype == TFSC_F32 && r.precision == TFSC_F32))))
+        return TFSC_ERR_UNSUPPORTED;
+    if (pix->links && (pix->rho || r.fresnel != TFSC_FRESNEL_PAPER ||
+                       !((pix->dtype == TFSC_F64 && r.precision == TFSC_F64) ||
+                         (pix->dtype == TFSC_F32 && r.precision == TFSC_F32))))
+        return TFSC_ERR_UNSUPPORTED;
+    hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+    if (bank->n == 0) return TFSC_OK;
+    tfsc::StatLaunch L = stat_launch(grid, pix, bank, seg, r, ws);
+    L.from_counter = from_counter;
+    if (r.schedule == TFSC_SCHED_WAVE && r.fresnel == TFSC_FRESNEL_PAPER && !pix->links && !from_counter)
+        use_split(grid, L, ws, ws_bytes, bank->ln_mc != nullptr);
+    if (tfsc::launch_prepare(L, pix->orbit, st) != hipSuccess) return TFSC_ERR_HIP;
+    L.seg_terms = seg_terms;
+    L.stat = stat;
+    L.seg_zn = seg_zn;
+    L.flags = flags;
+    L.n_active = n_active;
+    if (r.fresnel == TFSC_FRESNEL_ACCURATE) return hip_status(tfsc::launch_statistic_accurate(L, st));
+    if (pix->links) return hip_status(tfsc::launch_statistic_links(L, st));
+    return hip_status(tfsc::launch_statistic(L, st));
+}
+
 }  // namespace
 
 extern "C" {
@@ -327,40 +368,7 @@ tfsc_status tfsc_bank_statistic(const tfsc_grid *grid, const tfsc_pixels *pix, c
                                 const tfsc_segments *seg, const tfsc_options *opt, double *seg_terms, double *stat,
                                 double *seg_zn, int32_t *flags, int32_t *n_active, void *ws, size_t ws_bytes,
                                 void *stream) {
-    tfsc_status s;
-    if ((s = check_grid(grid)) != TFSC_OK) return s;
-    if ((s = check_bank(bank)) != TFSC_OK) return s;
-    if ((s = check_pixels(pix, bank->n > 0)) != TFSC_OK) return s;
-    if (!seg || (bank->n > 0 && (!seg->nseg || !seg->seg_offset))) return TFSC_ERR_ARG;
-    Resolved r;
-    if ((s = resolve_options(opt, pix, r)) != TFSC_OK) return s;
-    if (bank->n > 0 && (!seg_terms || !stat || !flags)) return TFSC_ERR_ARG;
-    if (!ws || ws_bytes < stat_ws_bytes(grid, bank->n, bank->ln_mc != nullptr)) return TFSC_ERR_WORKSPACE;
-    if (r.schedule == TFSC_SCHED_WAVE && pixel_store_bytes(grid, pix) > 0xffffffffull) return TFSC_ERR_UNSUPPORTED;
-    if (pix->rho && r.schedule == TFSC_SCHED_WAVE && pix->dtype != TFSC_F64 && pix->dtype != TFSC_F32)
-        return TFSC_ERR_UNSUPPORTED;
-    if (r.fresnel == TFSC_FRESNEL_ACCURATE &&
-        (pix->rho || !((pix->dtype == TFSC_F64 && r.precision == TFSC_F64) ||
-                       (pix->dtype == TFSC_F32 && r.precision == TFSC_F32))))
-        return TFSC_ERR_UNSUPPORTED;
-    if (pix->links && (pix->rho || r.fresnel != TFSC_FRESNEL_PAPER ||
-                       !((pix->dtype == TFSC_F64 && r.precision == TFSC_F64) ||
-                         (pix->dtype == TFSC_F32 && r.precision == TFSC_F32))))
-        return TFSC_ERR_UNSUPPORTED;
-    hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    if (bank->n == 0) return TFSC_OK;
-    tfsc::StatLaunch L = stat_launch(grid, pix, bank, seg, r, ws);
-    if (r.schedule == TFSC_SCHED_WAVE && r.fresnel == TFSC_FRESNEL_PAPER && !pix->links)
-        use_split(grid, L, ws, ws_bytes, bank->ln_mc != nullptr);
-    if (tfsc::launch_prepare(L, pix->orbit, st) != hipSuccess) return TFSC_ERR_HIP;
-    L.seg_terms = seg_terms;
-    L.stat = stat;
-    L.seg_zn = seg_zn;
-    L.flags = flags;
-    L.n_active = n_active;
-    if (r.fresnel == TFSC_FRESNEL_ACCURATE) return hip_status(tfsc::launch_statistic_accurate(L, st));
-    if (pix->links) return hip_status(tfsc::launch_statistic_links(L, st));
-    return hip_status(tfsc::launch_statistic(L, st));
+    return statistic_call(grid, pix, bank, seg, opt, seg_terms, stat, seg_zn, flags, n_active, ws, ws_bytes, stream, false);
 }
 
 tfsc_status tfsc_bank_statistic_noalloc(const tfsc_grid *grid, const tfsc_pixels *pix, const tfsc_bank *bank,
@@ -676,9 +684,11 @@ tfsc_status tfsc_tune_statistic(const tfsc_grid *grid, const tfsc_pixels *pix, c
         (void)hipEventDestroy(e0);
         return TFSC_ERR_HIP;
     }
-    // warm-up launch, with the full argument checks
-    tfsc_status s = tfsc_bank_statistic(grid, pix, bank, seg, &o, seg_terms, stat, nullptr, flags, nullptr, ws,
-                                        ws_bytes, stream);
+    // warm-up launch, with the full argument checks.  Whole templates from the counter: only the persistent grid depends
+    // on groups_per_cu, and it is what the shape is for in every call that is neither split nor in runs (a shape timed on
+    // a split tuning bank came out as 4x2 and slowed link tables from 163 to 197 ms, three harmonics from 408 to 501).
+    tfsc_status s = statistic_call(grid, pix, bank, seg, &o, seg_terms, stat, nullptr, flags, nullptr, ws, ws_bytes, stream,
+                                   true);
     float best = 0.0f;
     int bw = 0, gpc = 0;
     for (size_t c = 0; s == TFSC_OK && c < sizeof(kCand) / sizeof(kCand[0]); ++c) {
@@ -688,8 +698,8 @@ tfsc_status tfsc_tune_statistic(const tfsc_grid *grid, const tfsc_pixels *pix, c
         for (int rep = 0; rep < 2 && s == TFSC_OK; ++rep) {
             if (hipEventRecord(e0, st) != hipSuccess) s = TFSC_ERR_HIP;
             if (s == TFSC_OK)
-                s = tfsc_bank_statistic(grid, pix, bank, seg, &o, seg_terms, stat, nullptr, flags, nullptr, ws,
-                                        ws_bytes, stream);
+                s = statistic_call(grid, pix, bank, seg, &o, seg_terms, stat, nullptr, flags, nullptr, ws, ws_bytes,
+                                   stream, true);
             if (s == TFSC_OK && (hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess))
                 s = TFSC_ERR_HIP;
             float ms = 0.0f;

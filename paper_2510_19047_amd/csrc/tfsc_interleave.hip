@@ -102,10 +102,10 @@ __global__ __launch_bounds__(256, 3) void k_stat_wave_ri(StatArgs a) {
     const int lane = threadIdx.x & 63;
     const bool writer = lane == 0;
     for (bool more = true; more;) {
-        // with a processing order one template per wave in runs per XCD (run_item; up to kRunsMost of them), else one
+        // with a processing order one template per wave in runs per XCD (run_item; see in_runs), else one
         // atomic per wave on a uniform address, as in k_stat_wave
         int64_t i;
-        if (a.order && a.n <= kRunsMost) {
+        if (!PixTraits<PixT>::scaled && a.order && a.n <= kRunsMost) {
             int unit;
             const int64_t item = run_item(a.n, unit);
             if (item >= a.n || unit > 0) break;
@@ -275,10 +275,11 @@ hipError_t launch_statistic_interleaved(const StatLaunch &L, hipStream_t st) {
     if (tot > 0xffffffffull) return hipErrorInvalidValue;
     a.pix_bytes = (uint32_t)tot;
     a.seg_stride = L.seg_stride;
-    const int bw = L.block_waves;
+    const bool runs = L.order && in_runs(L.n, L.pix_dtype);
+    const int bw = runs ? kRunWaves : L.block_waves;
     int64_t groups = (L.n + bw - 1) / bw;
     if (groups > (int64_t)L.n_groups) groups = L.n_groups;
-    if (L.order && L.n <= kRunsMost) groups = run_groups(L.n, bw, 1);
+    if (runs) groups = run_groups(L.n, bw, 1);
     const int g = (int)groups;
     if (L.pix_dtype == 4) return dispatch_ri<int16_t>(L, a, g, bw, st);
     return dispatch_ri<float>(L, a, g, bw, st);

@@ -35,6 +35,13 @@ constexpr int kRecDoubles = 32;  // doubles of a template record
 // Most whole templates in runs, one wave each: a grid holds fewer than 2^32 threads, 67 million waves.  Larger banks in a
 // processing order take the persistent grid and its work counter.
 constexpr int64_t kRunsMost = 1 << 25;
+// Waves per block of these kernels, whatever block_waves says: a block stages the weight table for its waves' templates
+// only, not for all that a persistent wave goes through (1M templates, two years: 2 waves 131.8 ms, 4 waves 127.1).
+constexpr int kRunWaves = 4;
+// Runs are for FP32 and FP64 stores.  A 16-bit store's blocks would stage its layer scales as well, and its rows are half
+// as wide: 1M templates, two years, counter against runs: FP32 136.0 / 130.5 ms, but FP16 142.3 / 146.7, BF16 140.0 /
+// 143.7, I16 144.3 / 147.6; 4M templates x 16 realisations in pairs: FP32 5.49 / 5.18 s, I16 5.81 / 6.12.
+inline bool in_runs(int64_t n, int pix_dtype) { return n <= kRunsMost && pix_dtype <= 1; }
 struct SplitUnit {
     double zr, zi, N;  // sums of the segment that goes on into the next unit
     int code, m_end;   // flag and tranche of the track's end, if it ends in the unit (m_end: else the unit's end)
@@ -95,6 +102,7 @@ struct StatLaunch {
     int64_t seg_stride;   // elements between realisation planes of seg_terms
     int multi_group;      // realisations sharing one pass over the bank: 1, 2, 4 or 8
     SplitWs split;
+    bool from_counter;  // whole templates from the work counter also with a processing order
 };
 
 constexpr int kMultiGroupDefault = 8;

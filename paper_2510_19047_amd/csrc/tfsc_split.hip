@@ -143,7 +143,7 @@ static hipError_t launch_split_l(const StatArgs &a, int block_waves, hipStream_t
 
 template <int C, class R, class PixT>
 static hipError_t launch_split_t(const StatLaunch &L, const StatArgs &a, hipStream_t st) {
-    const int w = L.block_waves;
+    const int w = kRunWaves;
     if constexpr (!PixTraits<PixT>::scaled) {
         if (a.rho)
             return L.layout == 2 ? launch_split_l<C, R, PixT, 2, true>(a, w, st)

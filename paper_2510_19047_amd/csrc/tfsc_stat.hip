@@ -811,7 +811,8 @@ hipError_t launch_statistic_multi(const StatLaunch &L, hipStream_t st) {
 hipError_t launch_statistic(const StatLaunch &L, hipStream_t st) {
     StatArgs a = make_args(L);
     if (L.n == 0) return hipSuccess;
-    if (L.split.units || (L.schedule == 1 && L.order && L.n <= kRunsMost)) return launch_statistic_split(L, st);
+    const bool runs = L.schedule == 1 && L.order && in_runs(L.n, L.pix_dtype) && !L.from_counter;
+    if (L.split.units || runs) return launch_statistic_split(L, st);
     if (L.C == 1) return L.precision == 0 ? dispatch_pix<1, double>(L, a, st) : dispatch_pix<1, float>(L, a, st);
     if (L.C == 3) return L.precision == 0 ? dispatch_pix<3, double>(L, a, st) : dispatch_pix<3, float>(L, a, st);
     return L.precision == 0 ? dispatch_pix<2, double>(L, a, st) : dispatch_pix<2, float>(L, a, st);

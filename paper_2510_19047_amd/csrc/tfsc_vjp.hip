@@ -273,7 +273,7 @@ hipError_t launch_vjp(const VjpLaunch &V, hipStream_t st) {
     a.chunks = L.split.units ? L.split.chunks : (L.Nt + 63) / 64;
     a.rec = L.split.units ? L.split.rec : nullptr;
     a.part = reinterpret_cast<double *>(L.split.head);
-    if (a.units > 1) return launch_vjp_units(a, L.precision, L.C, L.pix_dtype, L.block_waves, st);
+    if (a.units > 1) return launch_vjp_units(a, L.precision, L.C, L.pix_dtype, kRunWaves, st);
     return L.precision == 1 ? dispatch_vjp_c<float>(a, L.counter, L.C, L.pix_dtype, L.n_groups, L.block_waves, st)
                             : dispatch_vjp_c<double>(a, L.counter, L.C, L.pix_dtype, L.n_groups, L.block_waves, st);
 }
