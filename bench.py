@@ -257,7 +257,7 @@ def main():
     traffic = None if prof is None else prof.get("traffic_bytes")
     roofline.update({
         "traffic": traffic,
-        "kernel": "k_stat_wave",
+        "kernel": "k_stat_wave" if order is None else "k_stat_runs",
         "kernel_ms": round(k_ms, 3),
         "profile_launch_shape": None if prof is None else prof.get("launch_shape"),
         "alg_bytes_per_launch": alg_bytes,
@@ -942,7 +942,9 @@ def batching_run(args, tfsc, ti, grid, g, psd_d, mu_d, keep_d, kw, chosen_ms_per
 
 
 PROFILE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "profiles", "k_stat_wave_counters.txt")
-STAT_SOURCES = ("tfsc_stat.hip", "tfsc_stat_common.hpp", "tfsc_device.hpp", "tfsc_kernels.hpp")
+STAT_SOURCES = ("tfsc_stat.hip", "tfsc_split.hip", "tfsc_stat_common.hpp", "tfsc_device.hpp", "tfsc_kernels.hpp")
+# the chosen form in a processing order, and the same wave kernel fetching templates from the work counter
+CHOSEN_KERNELS = ("k_stat_runs<2, float, float, 2, false>", "k_stat_wave<2, float, float, 2, false>")
 SIMDS = 1024                  # 256 CUs x 4 SIMDs
 NOMINAL_CLOCK_HZ = 2.4e9
 CYCLES_PER_VALU = 4           # a wave64 instruction on a 16-lane SIMD
@@ -959,7 +961,7 @@ def stat_source_sha256():
 
 
 def measured_profile(n, store, layout, order):
-    """Per-launch hardware counters of the chosen k_stat_wave launch from the committed rocprofv3 runs
+    """Per-launch hardware counters of the chosen statistic launch from the committed rocprofv3 runs
     (written by ``bench.py --summarize-counters``): calibrated bytes beyond L2, VALU instructions, the shader
     clock (GRBM_GUI_ACTIVE over the dispatch time) and the FP32/FP64 operation counts.
 
@@ -1033,12 +1035,13 @@ def alu_roofline(prof, k_s):
 
 def summarize_counters(dirs, n, store, layout, order, shape, fetch_factor, write_factor):
     """Write profiles/k_stat_wave_counters.txt from rocprofv3 --pmc CSV outputs (one directory per pass):
-    the median per dispatch of each counter over the chosen k_stat_wave launches after the first."""
+    the median per dispatch of each counter over the chosen statistic launches after the first."""
     import csv
     import glob
     vals = {}
     durs = []
     copy = {}
+    kernel = CHOSEN_KERNELS[0]
     for d in dirs:
         for path in glob.glob(os.path.join(d, "**", "*counter_collection.csv"), recursive=True):
             with open(path) as fh:
@@ -1050,8 +1053,10 @@ def summarize_counters(dirs, n, store, layout, order, shape, fetch_factor, write
                     # the 256 MiB device copy of --copy-calibration (the largest copy dispatch): bytes per KiB
                     k = row["Counter_Name"]
                     copy[k] = max(copy.get(k, 0.0), float(row["Counter_Value"]))
-                if "k_stat_wave<2, float, float, 2, false>" not in name:
+                chosen = [k for k in CHOSEN_KERNELS if k in name]
+                if not chosen:
                     continue
+                kernel = chosen[0]
                 by_disp.setdefault(int(row["Dispatch_Id"]), []).append(row)
             for disp in sorted(by_disp)[1:]:
                 for row in by_disp[disp]:
@@ -1060,10 +1065,10 @@ def summarize_counters(dirs, n, store, layout, order, shape, fetch_factor, write
                 if "Start_Timestamp" in r0 and "End_Timestamp" in r0:
                     durs.append(float(r0["End_Timestamp"]) - float(r0["Start_Timestamp"]))
     med = {k: float(np.median(v)) for k, v in vals.items()}
-    lines = ["# Read by bench.py: per-launch counters of the chosen k_stat_wave launch (median over the dispatches",
+    lines = ["# Read by bench.py: per-launch counters of the chosen statistic launch (median over the dispatches",
              "# after the first), valid only for this kernel source and workload; written by",
              "# python bench.py --summarize-counters <rocprofv3 --pmc output directories>",
-             "kernel: k_stat_wave<2, float, float, 2, false>",
+             f"kernel: {kernel}",
              f"source_sha256: {stat_source_sha256()}", f"n_templates: {n}", f"pixel_store: {store}",
              f"pixel_layout: {layout}", f"order: {order}", f"launch_shape: {shape}"]
     for k in sorted(med):
