@@ -373,26 +373,33 @@ constexpr float q_full = 1.0f;
 template <>
 constexpr float q_full<int16_t> = 32767.0f;
 
-// Scale and round the FP32 staging store, which has the final layout, to 16 bits: one streaming pass.  A block works
-// on one row of the layout (blockIdx.y): a layer (layout 0), a tranche of a channel (1) or the cells of a bin (2).
+// Scale and round the FP32 staging store, which has the final layout, to 16 bits: one streaming pass over the rows of the
+// layout: a layer (layout 0), a tranche of a channel (1) or the cells of a bin (2).  A block takes `per` rows of up to 256
+// elements each, or a part of a longer row; the blocks go over the groups of rows in gridDim.x (a tranche-major store has
+// C Nt rows, which no other grid dimension holds).
 template <class Q, int LAYOUT>
-__global__ __launch_bounds__(256) void k_quantize(int C, int K, int Nt, const float2 *__restrict__ st,
-                                                  const uint32_t *__restrict__ mx, float *__restrict__ layer_scale,
-                                                  Q *__restrict__ out) {
-    const int row = blockIdx.y, len = LAYOUT == 0 ? Nt : (LAYOUT == 1 ? K : Nt * C);
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < len; e += gridDim.x * blockDim.x) {
-        const int layer = LAYOUT == 0 ? row : (LAYOUT == 1 ? row / Nt * K + e : e % C * K + row);
-        const float m = __uint_as_float(mx[layer]);
-        const float inv = m > 0.0f ? q_full<Q> / m : 1.0f;
-        // one writer per layer: the first element of its row (its first tranche)
-        if (LAYOUT == 0 ? e == 0 : (LAYOUT == 1 ? row % Nt == 0 : e < C))
-            layer_scale[layer] = m > 0.0f ? m / q_full<Q> : 1.0f;
-        const size_t at = (size_t)row * len + e;
-        const float2 v = st[at];
-        struct alignas(4) Pair {
-            Q re, im;
-        };
-        reinterpret_cast<Pair *>(out)[at] = Pair{to_q<Q>(v.x * inv), to_q<Q>(v.y * inv)};
+__global__ __launch_bounds__(256) void k_quantize(int C, int K, int Nt, int rows, int len, int per, int parts,
+                                                  const float2 *__restrict__ st, const uint32_t *__restrict__ mx,
+                                                  float *__restrict__ layer_scale, Q *__restrict__ out) {
+    const int in_group = per > 1 ? (int)threadIdx.x / len : 0;
+    const int e0 = per > 1 ? (int)threadIdx.x - in_group * len : (int)(blockIdx.x % parts) * 256 + (int)threadIdx.x;
+    const int step = (int)(gridDim.x / parts) * per;
+    if (in_group >= per) return;
+    for (int row = (int)(blockIdx.x / parts) * per + in_group; row < rows; row += step) {
+        for (int e = e0; e < len; e += parts * 256) {
+            const int layer = LAYOUT == 0 ? row : (LAYOUT == 1 ? row / Nt * K + e : e % C * K + row);
+            const float m = __uint_as_float(mx[layer]);
+            const float inv = m > 0.0f ? q_full<Q> / m : 1.0f;
+            // one writer per layer: the first element of its row (its first tranche)
+            if (LAYOUT == 0 ? e == 0 : (LAYOUT == 1 ? row % Nt == 0 : e < C))
+                layer_scale[layer] = m > 0.0f ? m / q_full<Q> : 1.0f;
+            const size_t at = (size_t)row * len + e;
+            const float2 v = st[at];
+            struct alignas(4) Pair {
+                Q re, im;
+            };
+            reinterpret_cast<Pair *>(out)[at] = Pair{to_q<Q>(v.x * inv), to_q<Q>(v.y * inv)};
+        }
     }
 }
 
@@ -494,15 +501,20 @@ static hipError_t run_quantize(const TransformLaunch &L, const uint32_t *mx, hip
     const int K = L.M / 2 + 1;
     const int rows = L.out_layout == 0 ? L.C * K : (L.out_layout == 1 ? L.C * L.Nt : K);
     const int len = L.out_layout == 0 ? L.Nt : (L.out_layout == 1 ? K : L.Nt * L.C);
-    const dim3 g((unsigned)((len + 255) / 256 > 8 ? 8 : (len + 255) / 256), (unsigned)rows);
+    const int per = len < 256 ? 256 / len : 1, parts = (len + 255) / 256 > 8 ? 8 : (len + 255) / 256;
+    const int groups = (rows + per - 1) / per, most = 1 << 20;  // blocks of 256 threads: below 2^32 in all
+    const dim3 g((unsigned)((groups < most ? groups : most) * parts));
     const float2 *src = reinterpret_cast<const float2 *>(L.ws);
     Q *out = reinterpret_cast<Q *>(L.pix);
     if (L.out_layout == 0)
-        hipLaunchKernelGGL((k_quantize<Q, 0>), g, dim3(256), 0, st, L.C, K, L.Nt, src, mx, L.layer_scale, out);
+        hipLaunchKernelGGL((k_quantize<Q, 0>), g, dim3(256), 0, st, L.C, K, L.Nt, rows, len, per, parts, src, mx,
+                           L.layer_scale, out);
     else if (L.out_layout == 1)
-        hipLaunchKernelGGL((k_quantize<Q, 1>), g, dim3(256), 0, st, L.C, K, L.Nt, src, mx, L.layer_scale, out);
+        hipLaunchKernelGGL((k_quantize<Q, 1>), g, dim3(256), 0, st, L.C, K, L.Nt, rows, len, per, parts, src, mx,
+                           L.layer_scale, out);
     else
-        hipLaunchKernelGGL((k_quantize<Q, 2>), g, dim3(256), 0, st, L.C, K, L.Nt, src, mx, L.layer_scale, out);
+        hipLaunchKernelGGL((k_quantize<Q, 2>), g, dim3(256), 0, st, L.C, K, L.Nt, rows, len, per, parts, src, mx,
+                           L.layer_scale, out);
     return hipGetLastError();
 }
 

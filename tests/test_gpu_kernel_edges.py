@@ -91,6 +91,29 @@ def test_transform_into_a_store_off_16_bytes():
     assert torch.equal(a.pix, b.pix) and float(flat[:2].abs().max()) == 0.0
 
 
+@pytest.mark.parametrize("C, M, Nt", [(2, 64, 33_000), (3, 128, 22_001), (1, 512, 66_000)])
+@pytest.mark.parametrize("layout", ["tranche", "layer"])
+def test_sixteen_bit_store_of_many_tranches(C, M, Nt, layout):
+    """More than 65,536 tranche-major rows (shorter and longer than a block of the quantisation): the 16-bit store holds
+    the nearest integer to each FP32 pixel over its layer's scale, which is the layer's largest FP32 component over
+    32767.  The division by the scale is a multiplication there: at most one step apart where it rounds."""
+    tfsc = lib()
+    grid = tfsc.GridSpec(C, M, Nt, 5.0, 0.1)
+    gen = torch.Generator(device="cuda").manual_seed(C)
+    x = torch.randn((C, M * Nt), generator=gen, device="cuda")
+    args = (dev(np.ones(M // 2 + 1)), dev(np.ones(Nt)), dev(np.ones(Nt, np.uint8)))
+    note(f"16-bit store C={C} M={M} Nt={Nt} {layout}")
+    a = tfsc.transform(grid, x, *args, dtype="f32", layout=layout)
+    b = tfsc.transform(grid, x, *args, dtype="i16", layout=layout)
+    p = (a.pix if layout == "layer" else a.pix.transpose(1, 2)).double()  # [C][K][Nt][2]
+    q = (b.pix if layout == "layer" else b.pix.transpose(1, 2)).double()
+    top = p.abs().amax(dim=(2, 3))
+    assert float((b.layer_scale.double() * 32767.0 / top - 1.0).abs().max()) < 2.0 ** -23
+    want = p * (32767.0 / top)[:, :, None, None]
+    # half a step, and the float rounding of the factor and of the product (2^-24 each of at most 32767)
+    assert float((q - want).abs().max()) <= 0.5 + 2.0 * 32767.0 * 2.0 ** -24
+
+
 def _bank(tfsc, n, seed):
     b = ti.random_bank(n, seed, mc_range=(5.0, 100.0), f0_range=(0.004, 0.08), eta=None, stream=62)
     if n > 20:
