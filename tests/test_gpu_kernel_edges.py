@@ -114,6 +114,24 @@ def test_sixteen_bit_store_of_many_tranches(C, M, Nt, layout):
     assert float((q - want).abs().max()) <= 0.5 + 2.0 * 32767.0 * 2.0 ** -24
 
 
+@pytest.mark.parametrize("C, M, Nt", [(1, 64, 1), (2, 128, 3), (2, 2048, 1), (1, 4096, 3)])
+@pytest.mark.parametrize("layout", ["layer_ci", "tranche"])
+def test_layer_scale_is_the_maximum_of_stored_pixels(C, M, Nt, layout):
+    """An odd number of tranches of a sinusoid on a bin: in most layers all pixels are of rounding size, and the scale of
+    the 16-bit store is the largest of them, exactly (the FP32 store holds the same FP32 values; the maximum divided by
+    32767 is one rounding); where all of them are zero it is 1."""
+    tfsc = lib()
+    grid = tfsc.GridSpec(C, M, Nt, 5.0, 0.0)
+    note(f"layer scale C={C} M={M} Nt={Nt} {layout}")
+    x = dev(np.tile(np.cos(2.0 * np.pi * (M // 8) * np.arange(M) / M + 0.3), (C, Nt)).astype(np.float32))
+    args = (dev(np.ones(M // 2 + 1)), dev(np.ones(Nt)), dev(np.ones(Nt, np.uint8)))
+    p = tfsc.transform(grid, x, *args, dtype="f32", layout=layout).pix
+    top = {"layer_ci": lambda v: v.abs().amax(dim=(1, 3)).T, "tranche": lambda v: v.abs().amax(dim=(1, 3))}[layout](p)
+    got = tfsc.transform(grid, x, *args, dtype="i16", layout=layout).layer_scale
+    top = top.cpu().numpy()  # numpy's division is correctly rounded; torch divides by a number with its reciprocal
+    assert np.array_equal(got.cpu().numpy(), np.where(top > 0, top / np.float32(32767.0), np.float32(1.0)))
+
+
 def _bank(tfsc, n, seed):
     b = ti.random_bank(n, seed, mc_range=(5.0, 100.0), f0_range=(0.004, 0.08), eta=None, stream=62)
     if n > 20:
