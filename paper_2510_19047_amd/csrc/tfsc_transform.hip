@@ -44,17 +44,18 @@ __device__ __forceinline__ cx<float> twiddle<float>(double frac) {
 //
 // The first stages take their points from the series itself; the last exchange puts Z in natural order for the split
 // of the two tranches.  A thread keeps the whitened values of NIT transforms (a pair of tranches of each of the CC
-// channels of a cell, or two pairs of one channel) and writes a run of at least 32 bytes per frequency layer, NF times
-// per block.  Each group's largest values of a 16-bit store's layers meet in LDS before the global atomics: with one
-// atomic per layer and group they queued up at the few addresses of a small M (A+E, M = 128, 60,000 tranches, 16 bits:
-// 2528 us a call, now 105).  Consecutive tiles go to one XCD, whose L2 joins the runs of neighbouring tiles (113.7 MB written for a
-// 100.8 MB store).
+// channels of a cell, or NIT pairs of one channel) and writes a run of 16 or 32 bytes per frequency layer.  Consecutive
+// tiles go to one XCD, whose L2 joins the runs of neighbouring tiles.  Each group's largest values of a 16-bit store's
+// layers meet in LDS before the global atomics: with one atomic per layer and group they queued up at the few addresses of
+// a small M (A+E, M = 128, 60,000 tranches, 16 bits: 2528 us a call, now 100).
 //
-// Bound: latency, at three waves per SIMD (the registers and 53 KB of LDS allow no more); the vector ALU is busy for
-// half the time, the LDS for a third.  Two years of A+E, FP32 (100.7 MB in, 100.8 MB out): 87 us, 2.3 TB/s, against
-// 520 us with one exchange per stage, a branch (and a wait) around every load and 8-byte stores.  Holding the runs of
-// four tranches or the window in registers across the transforms spilled and took 139-168 us; forming the whitening
-// factors (a division and a square root per bin and tranche, 40% of the instructions) for each channel anew, 97 us.
+// Bound: latency, at three to four waves per SIMD (53 KB of LDS at M = 2048 allow three blocks a CU).  Two years of A+E,
+// FP32 (100.7 MB in, 100.8 MB out): 80 us, 2.5 TB/s, against 520 us with one exchange per stage, a branch (and a wait)
+// around every load and 8-byte stores.  With a loop over two such runs in a block the transforms' registers passed 150 and
+// a few spilled: 87 us, and short sets waited for twice the work (A+E, M = 1024, 33 tranches: 21 us a call against 14).
+// Holding the runs of four tranches or the window in registers across the transforms spilled and took 139-168 us; forming
+// the whitening factors (a division and a square root per bin and tranche) for each channel anew, 10 us more.
+//
 // -i w: the twiddle a quarter turn on.  For a twiddle below exp(-i pi / 4) it has the table's bits; from there on the
 // table's own entry is read (its sine and cosine of pi / 4 differ in the last place).
 template <class R>
@@ -77,7 +78,7 @@ struct alignas(2 * sizeof(R)) lds_cx {
     __device__ __forceinline__ operator cx<R>() const { return {re, im}; }
 };
 
-// Padding: one element in 8 (the stage outputs lie 8 apart), one in 16 for the twiddles.  The lanes' positions are
+// Padding: one element in 8 (the stage outputs lie 8 apart), one in 64 for the twiddles.  The lanes' positions are
 // base + constant, so that every offset is an immediate of the access.
 __host__ __device__ constexpr int lds_pos(int i) { return i + (i >> 3); }
 __host__ __device__ constexpr int tw_pos(int i) { return i + (i >> 6); }
@@ -121,7 +122,7 @@ __device__ __forceinline__ void load8(cx<R> (&v)[8], const lds_cx<R> *buf, int t
 // One block's transforms: CC channels (1, or all of a channel-interleaved cell) of TB tranches per group of M/8
 // threads.  Tranches are transformed in pairs, z = x_m + i x_{m+1}: X_m[k] = (Z[k] + conj Z[M-k]) / 2 and
 // X_{m+1}[k] = (Z[k] - conj Z[M-k]) / (2i).
-template <class R, class XT, class OutT, int M, int CC, int NIT, int NF>
+template <class R, class XT, class OutT, int M, int CC, int NIT>
 __global__ __launch_bounds__(M == 4096 ? 512 : 256, CC == 3 ? 2 : 3) void k_transform(
     TransformLaunch L, double w2, int width, uint32_t *__restrict__ layer_max, int n_tiles) {
     constexpr int TB = 2 * NIT / CC;  // tranches per group
@@ -131,7 +132,7 @@ __global__ __launch_bounds__(M == 4096 ? 512 : 256, CC == 3 ? 2 : 3) void k_tran
     const int Nt = L.Nt;
     const int t0 = threadIdx.x & (T8 - 1), grp = threadIdx.x / T8;
     lds_cx<R> *buf = bufs + grp * lds_pos(M);
-    uint32_t *top = reinterpret_cast<uint32_t *>(bufs);  // [NG][CC][K] after a turn's transforms: the groups' layer maxima
+    uint32_t *top = reinterpret_cast<uint32_t *>(bufs);  // [NG][CC][K] after the transforms: the groups' layer maxima
     for (int k = threadIdx.x; k < M / 2; k += NT) {
         const cx<R> w = twiddle<R>((double)k / M);
         tw[tw_pos(k)] = {w.re, w.im};
@@ -152,222 +153,219 @@ __global__ __launch_bounds__(M == 4096 ? 512 : 256, CC == 3 ? 2 : 3) void k_tran
     auto psd = [&](int k, int mj, double mu) -> double {  // mj < Nt
         return L.psd_tf ? L.psd_tf[(size_t)k * Nt + mj] : L.psd0[k] * mu;
     };
-#pragma unroll 1
-    for (int fl = 0; fl < NF; ++fl) {
-        const int m0 = ((tile * NF + fl) * NG + grp) * TB;
-        // held[it][i][tr]: bin k = t + i M/8 of tranche m + tr; DC and Nyquist are real, so bin 0 holds (DC, Nyquist)
-        cx<OutT> held[NIT][4][2] = {};
-        R sc[4][2], scn[2];
-        // a cell's channels one after the other without a loop, so that the pair's whitening factors and the values
-        // held live only as long as they must; of one channel the loop stays (unrolled it would spill)
-        constexpr int kUnroll = CC == 1 ? 1 : NIT;
+    const int m0 = (tile * NG + grp) * TB;
+    // held[it][i][tr]: bin k = t + i M/8 of tranche m + tr; DC and Nyquist are real, so bin 0 holds (DC, Nyquist)
+    cx<OutT> held[NIT][4][2] = {};
+    R sc[4][2], scn[2];
+    // a cell's channels one after the other without a loop, so that the pair's whitening factors and the values
+    // held live only as long as they must; of one channel the loop stays (unrolled it would spill)
+    constexpr int kUnroll = CC == 1 ? 1 : NIT;
 #pragma unroll kUnroll
-        for (int it = 0; it < NIT; ++it) {
-            const int c = c0 + it % CC, m = m0 + 2 * (it / CC);
-            // the thread's index anew for each transform: the addresses, window and PSD values that depend on it are then
-            // formed where they are used instead of being held in registers (and spilled) across the transforms
-            int t = t0;
-            asm volatile("" : "+v"(t));
-            cx<R> v[8];
-            {
-                // tranches past the end read the last one and count as zero
-                const int ma = min(m, Nt - 1), mb = min(m + 1, Nt - 1);
-                const XT *xa = reinterpret_cast<const XT *>(L.x) + ((size_t)c * Nt + ma) * M + t;
-                const XT *xb = reinterpret_cast<const XT *>(L.x) + ((size_t)c * Nt + mb) * M + t;
-                XT a[8], b[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    a[i] = xa[i * T8];
-                    b[i] = xb[i * T8];
-                }
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const R win = tukey_w<R>(t + i * T8, M, L.alpha, width);
-                    v[i].re = m < Nt ? (R)a[i] * win : (R)0;
-                    v[i].im = m + 1 < Nt ? (R)b[i] * win : (R)0;
-                }
-            }
-            __syncthreads();  // the twiddles are there, and the last transform's split has read its points
-            stages3<M, 1>(v, tw, 0);
-            store8<1>(v, buf, t, 0);
-            __syncthreads();
-            load8<T8>(v, buf, t);
-            stages3<M, 8>(v, tw, t & 7);
-            __syncthreads();
-            store8<8>(v, buf, t, t & 7);
-            __syncthreads();
-            if constexpr (M >= 512) {
-                load8<T8>(v, buf, t);
-                stages3<M, 64>(v, tw, t & 63);
-                __syncthreads();
-                store8<64>(v, buf, t, t & 63);
-                __syncthreads();
-            }
-            if constexpr (M >= 4096) {
-                load8<T8>(v, buf, t);
-                stages3<M, 512>(v, tw, t & 511);
-                __syncthreads();
-                store8<512>(v, buf, t, t & 511);
-                __syncthreads();
-            }
-            constexpr int LEFT = M >= 512 ? (M >= 4096 ? M / 4096 : M / 512) : M / 64;  // stages left: 1, 2 or 4 points
-            if constexpr (LEFT == 2) {
-                constexpr int NS = M / 2;
-                load8<T8>(v, buf, t);
-                __syncthreads();
-                lds_cx<R> *p = buf + lds_pos(t);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    butterfly(v[i], v[i + 4], (cx<R>)tw[tw_pos(t + i * T8)]);
-                    p[lds_pos(i * T8)] = {v[i].re, v[i].im};
-                    p[lds_pos(i * T8 + NS)] = {v[i + 4].re, v[i + 4].im};
-                }
-                __syncthreads();
-            } else if constexpr (LEFT == 4) {
-                constexpr int NS = M / 4;
-                load8<T8>(v, buf, t);
-                __syncthreads();
-                lds_cx<R> *p = buf + lds_pos(t);
-#pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    const int kk = t + i * T8;  // < NS
-                    const cx<R> wa = tw[tw_pos(2 * kk)], wb = tw[tw_pos(kk)], wbi = tw[tw_pos(kk + NS)];
-                    butterfly(v[i], v[i + 4], wa);
-                    butterfly(v[i + 2], v[i + 6], wa);
-                    butterfly(v[i], v[i + 2], wb);        // b0 = 0: outputs 0 and 2
-                    butterfly(v[i + 4], v[i + 6], wbi);   // b0 = 1: outputs 1 and 3
-                    p[lds_pos(i * T8)] = {v[i].re, v[i].im};
-                    p[lds_pos(i * T8 + NS)] = {v[i + 4].re, v[i + 4].im};
-                    p[lds_pos(i * T8 + 2 * NS)] = {v[i + 2].re, v[i + 2].im};
-                    p[lds_pos(i * T8 + 3 * NS)] = {v[i + 6].re, v[i + 6].im};
-                }
-                __syncthreads();
-            }
-            // the whitening factors of the pair, where the transform's registers are free
+    for (int it = 0; it < NIT; ++it) {
+        const int c = c0 + it % CC, m = m0 + 2 * (it / CC);
+        // the thread's index anew for each transform: the addresses, window and PSD values that depend on it are then
+        // formed where they are used instead of being held in registers (and spilled) across the transforms
+        int t = t0;
+        asm volatile("" : "+v"(t));
+        cx<R> v[8];
+        {
+            // tranches past the end read the last one and count as zero
             const int ma = min(m, Nt - 1), mb = min(m + 1, Nt - 1);
-            const double mua = L.psd_tf ? 1.0 : L.mu[ma], mub = L.psd_tf ? 1.0 : L.mu[mb];
-            const bool ka = L.keep[ma] != 0, kb = L.keep[mb] != 0;
-            if (it % CC == 0) {
-                double sa[4], sb[4];
+            const XT *xa = reinterpret_cast<const XT *>(L.x) + ((size_t)c * Nt + ma) * M + t;
+            const XT *xb = reinterpret_cast<const XT *>(L.x) + ((size_t)c * Nt + mb) * M + t;
+            XT a[8], b[8];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    sa[i] = psd(t + i * T8, ma, mua);
-                    sb[i] = psd(t + i * T8, mb, mub);
-                }
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    sc[i][0] = scale(sa[i], ka);
-                    sc[i][1] = scale(sb[i], kb);
-                }
-                if (t == 0) {
-                    scn[0] = scale(psd(M / 2, ma, mua), ka);
-                    scn[1] = scale(psd(M / 2, mb, mub), kb);
-                }
+            for (int i = 0; i < 8; ++i) {
+                a[i] = xa[i * T8];
+                b[i] = xb[i * T8];
             }
-            // the oldest transform's values stand first after the last turn
 #pragma unroll
-            for (int q = 0; q + 1 < NIT; ++q)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    held[q][i][0] = held[q + 1][i][0];
-                    held[q][i][1] = held[q + 1][i][1];
-                }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int k = t + i * T8;
-                const cx<R> zk = buf[lds_pos(t) + lds_pos(i * T8)], zn = buf[lds_pos((M - k) & (M - 1))];
-                cx<R> X[2] = {{(R)0.5 * (zk.re + zn.re), (R)0.5 * (zk.im - zn.im)},
-                              {(R)0.5 * (zk.im + zn.im), (R)0.5 * (zn.re - zk.re)}};
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    cx<R> o = cscale(X[j], sc[i][j]);
-                    if (i == 0 && t == 0) {
-                        const cx<R> zq = buf[lds_pos(M / 2)];
-                        o.im = (j == 0 ? zq.re : zq.im) * scn[j];
-                    }
-                    held[NIT - 1][i][j] = {(OutT)o.re, (OutT)o.im};
-                }
+            for (int i = 0; i < 8; ++i) {
+                const R win = tukey_w<R>(t + i * T8, M, L.alpha, width);
+                v[i].re = m < Nt ? (R)a[i] * win : (R)0;
+                v[i].im = m + 1 < Nt ? (R)b[i] * win : (R)0;
             }
         }
-
-        OutT *pix = reinterpret_cast<OutT *>(L.pix);
-        auto put = [&](int k, int q, int j, cx<OutT> o) {  // the pixel of transform q, tranche j of its pair
-            const int c = c0 + q % CC, m = m0 + 2 * (q / CC) + j;
-            if (m >= Nt) return;
-            const size_t idx = L.out_layout == 0   ? ((size_t)c * K + k) * Nt + m
-                               : L.out_layout == 1 ? ((size_t)c * Nt + m) * K + k
-                                                   : ((size_t)k * Nt + m) * L.C + c;
-            reinterpret_cast<cx<OutT> *>(pix)[idx] = o;
-        };
-        // one 16-byte store per FP32 A+E cell
-        auto put_cells = [&](int k, const cx<OutT> (&a)[2], const cx<OutT> (&b)[2], int q) {
+        __syncthreads();  // the twiddles are there, and the last transform's split has read its points
+        stages3<M, 1>(v, tw, 0);
+        store8<1>(v, buf, t, 0);
+        __syncthreads();
+        load8<T8>(v, buf, t);
+        stages3<M, 8>(v, tw, t & 7);
+        __syncthreads();
+        store8<8>(v, buf, t, t & 7);
+        __syncthreads();
+        if constexpr (M >= 512) {
+            load8<T8>(v, buf, t);
+            stages3<M, 64>(v, tw, t & 63);
+            __syncthreads();
+            store8<64>(v, buf, t, t & 63);
+            __syncthreads();
+        }
+        if constexpr (M >= 4096) {
+            load8<T8>(v, buf, t);
+            stages3<M, 512>(v, tw, t & 511);
+            __syncthreads();
+            store8<512>(v, buf, t, t & 511);
+            __syncthreads();
+        }
+        constexpr int LEFT = M >= 512 ? (M >= 4096 ? M / 4096 : M / 512) : M / 64;  // stages left: 1, 2 or 4 points
+        if constexpr (LEFT == 2) {
+            constexpr int NS = M / 2;
+            load8<T8>(v, buf, t);
+            __syncthreads();
+            lds_cx<R> *p = buf + lds_pos(t);
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int m = m0 + 2 * (q / CC) + j;
-                if (m >= Nt) continue;
-                reinterpret_cast<float4 *>(pix)[(size_t)k * Nt + m] =
-                    float4{(float)a[j].re, (float)a[j].im, (float)b[j].re, (float)b[j].im};
+            for (int i = 0; i < 4; ++i) {
+                butterfly(v[i], v[i + 4], (cx<R>)tw[tw_pos(t + i * T8)]);
+                p[lds_pos(i * T8)] = {v[i].re, v[i].im};
+                p[lds_pos(i * T8 + NS)] = {v[i + 4].re, v[i + 4].im};
             }
-        };
-        auto put_row = [&](int k, const cx<OutT> (&row)[NIT][2]) {
-            if constexpr (CC == 2 && sizeof(OutT) == 4) {
+            __syncthreads();
+        } else if constexpr (LEFT == 4) {
+            constexpr int NS = M / 4;
+            load8<T8>(v, buf, t);
+            __syncthreads();
+            lds_cx<R> *p = buf + lds_pos(t);
 #pragma unroll
-                for (int q = 0; q < NIT; q += 2) put_cells(k, row[q], row[q + 1], q);
-            } else {
-#pragma unroll
-                for (int q = 0; q < NIT; ++q)
-#pragma unroll
-                    for (int j = 0; j < 2; ++j) put(k, q, j, row[q][j]);
+            for (int i = 0; i < 2; ++i) {
+                const int kk = t + i * T8;  // < NS
+                const cx<R> wa = tw[tw_pos(2 * kk)], wb = tw[tw_pos(kk)], wbi = tw[tw_pos(kk + NS)];
+                butterfly(v[i], v[i + 4], wa);
+                butterfly(v[i + 2], v[i + 6], wa);
+                butterfly(v[i], v[i + 2], wb);        // b0 = 0: outputs 0 and 2
+                butterfly(v[i + 4], v[i + 6], wbi);   // b0 = 1: outputs 1 and 3
+                p[lds_pos(i * T8)] = {v[i].re, v[i].im};
+                p[lds_pos(i * T8 + NS)] = {v[i + 4].re, v[i + 4].im};
+                p[lds_pos(i * T8 + 2 * NS)] = {v[i + 2].re, v[i + 2].im};
+                p[lds_pos(i * T8 + 3 * NS)] = {v[i + 6].re, v[i + 6].im};
             }
-            if constexpr (sizeof(OutT) == 4)
-                if (layer_max) {
+            __syncthreads();
+        }
+        // the whitening factors of the pair, where the transform's registers are free
+        const int ma = min(m, Nt - 1), mb = min(m + 1, Nt - 1);
+        const double mua = L.psd_tf ? 1.0 : L.mu[ma], mub = L.psd_tf ? 1.0 : L.mu[mb];
+        const bool ka = L.keep[ma] != 0, kb = L.keep[mb] != 0;
+        if (it % CC == 0) {
+            double sa[4], sb[4];
 #pragma unroll
-                    for (int cc = 0; cc < CC; ++cc) {
-                        float mx = 0.0f;
+            for (int i = 0; i < 4; ++i) {
+                sa[i] = psd(t + i * T8, ma, mua);
+                sb[i] = psd(t + i * T8, mb, mub);
+            }
 #pragma unroll
-                        for (int q = cc; q < NIT; q += CC)
+            for (int i = 0; i < 4; ++i) {
+                sc[i][0] = scale(sa[i], ka);
+                sc[i][1] = scale(sb[i], kb);
+            }
+            if (t == 0) {
+                scn[0] = scale(psd(M / 2, ma, mua), ka);
+                scn[1] = scale(psd(M / 2, mb, mub), kb);
+            }
+        }
+        // the oldest transform's values stand first after the last turn
 #pragma unroll
-                            for (int j = 0; j < 2; ++j)
-                                if (m0 + 2 * (q / CC) + j < Nt)
-                                    mx = fmaxf(fmaxf(mx, fabsf((float)row[q][j].re)), fabsf((float)row[q][j].im));
-                        if constexpr (NG == 1)
-                            atomicMax(layer_max + (size_t)(c0 + cc) * K + k, __float_as_uint(mx));
-                        else
-                            top[(grp * CC + cc) * K + k] = __float_as_uint(mx);
-                    }
-                }
-        };
-        if (NG > 1 && layer_max) __syncthreads();  // the last transform's split has read its points
+        for (int q = 0; q + 1 < NIT; ++q)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                held[q][i][0] = held[q + 1][i][0];
+                held[q][i][1] = held[q + 1][i][1];
+            }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int k = t0 + i * T8;
-            cx<OutT> row[NIT][2];
+            const int k = t + i * T8;
+            const cx<R> zk = buf[lds_pos(t) + lds_pos(i * T8)], zn = buf[lds_pos((M - k) & (M - 1))];
+            cx<R> X[2] = {{(R)0.5 * (zk.re + zn.re), (R)0.5 * (zk.im - zn.im)},
+                          {(R)0.5 * (zk.im + zn.im), (R)0.5 * (zn.re - zk.re)}};
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                cx<R> o = cscale(X[j], sc[i][j]);
+                if (i == 0 && t == 0) {
+                    const cx<R> zq = buf[lds_pos(M / 2)];
+                    o.im = (j == 0 ? zq.re : zq.im) * scn[j];
+                }
+                held[NIT - 1][i][j] = {(OutT)o.re, (OutT)o.im};
+            }
+        }
+    }
+
+    OutT *pix = reinterpret_cast<OutT *>(L.pix);
+    auto put = [&](int k, int q, int j, cx<OutT> o) {  // the pixel of transform q, tranche j of its pair
+        const int c = c0 + q % CC, m = m0 + 2 * (q / CC) + j;
+        if (m >= Nt) return;
+        const size_t idx = L.out_layout == 0   ? ((size_t)c * K + k) * Nt + m
+                           : L.out_layout == 1 ? ((size_t)c * Nt + m) * K + k
+                                               : ((size_t)k * Nt + m) * L.C + c;
+        reinterpret_cast<cx<OutT> *>(pix)[idx] = o;
+    };
+    // one 16-byte store per FP32 A+E cell
+    auto put_cells = [&](int k, const cx<OutT> (&a)[2], const cx<OutT> (&b)[2], int q) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int m = m0 + 2 * (q / CC) + j;
+            if (m >= Nt) continue;
+            reinterpret_cast<float4 *>(pix)[(size_t)k * Nt + m] =
+                float4{(float)a[j].re, (float)a[j].im, (float)b[j].re, (float)b[j].im};
+        }
+    };
+    auto put_row = [&](int k, const cx<OutT> (&row)[NIT][2]) {
+        if constexpr (CC == 2 && sizeof(OutT) == 4) {
+#pragma unroll
+            for (int q = 0; q < NIT; q += 2) put_cells(k, row[q], row[q + 1], q);
+        } else {
 #pragma unroll
             for (int q = 0; q < NIT; ++q)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) row[q][j] = held[q][i][j];
-            if (i == 0 && t0 == 0) {
-                cx<OutT> nyq[NIT][2];
-#pragma unroll
-                for (int q = 0; q < NIT; ++q)
-#pragma unroll
-                    for (int j = 0; j < 2; ++j) {
-                        const cx<OutT> o = row[q][j];
-                        nyq[q][j] = {o.im, o.im - o.im};
-                        row[q][j] = {o.re, o.re - o.re};
-                    }
-                put_row(M / 2, nyq);
-            }
-            put_row(k, row);
+                for (int j = 0; j < 2; ++j) put(k, q, j, row[q][j]);
         }
-        if (NG > 1 && layer_max) {
-            // the groups' maxima of a layer go out as one
-            __syncthreads();
-            for (int q = threadIdx.x; q < CC * K; q += NT) {
-                uint32_t mx = top[q];
-                for (int g = 1; g < NG; ++g) mx = max(mx, top[g * CC * K + q]);
-                atomicMax(layer_max + (size_t)c0 * K + q, mx);
+        if constexpr (sizeof(OutT) == 4)
+            if (layer_max) {
+#pragma unroll
+                for (int cc = 0; cc < CC; ++cc) {
+                    float mx = 0.0f;
+#pragma unroll
+                    for (int q = cc; q < NIT; q += CC)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            if (m0 + 2 * (q / CC) + j < Nt)
+                                mx = fmaxf(fmaxf(mx, fabsf((float)row[q][j].re)), fabsf((float)row[q][j].im));
+                    if constexpr (NG == 1)
+                        atomicMax(layer_max + (size_t)(c0 + cc) * K + k, __float_as_uint(mx));
+                    else
+                        top[(grp * CC + cc) * K + k] = __float_as_uint(mx);
+                }
             }
+    };
+    if (NG > 1 && layer_max) __syncthreads();  // the last transform's split has read its points
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int k = t0 + i * T8;
+        cx<OutT> row[NIT][2];
+#pragma unroll
+        for (int q = 0; q < NIT; ++q)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) row[q][j] = held[q][i][j];
+        if (i == 0 && t0 == 0) {
+            cx<OutT> nyq[NIT][2];
+#pragma unroll
+            for (int q = 0; q < NIT; ++q)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const cx<OutT> o = row[q][j];
+                    nyq[q][j] = {o.im, o.im - o.im};
+                    row[q][j] = {o.re, o.re - o.re};
+                }
+            put_row(M / 2, nyq);
+        }
+        put_row(k, row);
+    }
+    if (NG > 1 && layer_max) {
+        // the groups' maxima of a layer go out as one
+        __syncthreads();
+        for (int q = threadIdx.x; q < CC * K; q += NT) {
+            uint32_t mx = top[q];
+            for (int g = 1; g < NG; ++g) mx = max(mx, top[g * CC * K + q]);
+            atomicMax(layer_max + (size_t)c0 * K + q, mx);
         }
     }
 }
@@ -472,45 +470,60 @@ static double window_w2(int M, double alpha) {
     return s / M;
 }
 
-template <class R, class XT, class OutT, int M, int CC, int NIT, int NF>
+template <class R, class XT, class OutT, int M, int CC, int NIT>
 static hipError_t run_fft_m(const TransformLaunch &L, double w2, uint32_t *layer_max, hipStream_t st) {
     const int threads = M == 4096 ? 512 : 256, n_grp = threads / (M / 8);
-    const int per_block = NF * n_grp * (2 * NIT / CC), n_tiles = (L.Nt + per_block - 1) / per_block;
+    const int per_block = n_grp * (2 * NIT / CC), n_tiles = (L.Nt + per_block - 1) / per_block;
     const dim3 grid((unsigned)((n_tiles + 7) / 8 * 8), (unsigned)(L.C / CC));
     const int width = L.alpha > 0.0 ? (int)floor(L.alpha * (M - 1) / 2.0) : -1;
-    hipLaunchKernelGGL((k_transform<R, XT, OutT, M, CC, NIT, NF>), grid, dim3(threads), 0, st, L, w2, width, layer_max, n_tiles);
+    hipLaunchKernelGGL((k_transform<R, XT, OutT, M, CC, NIT>), grid, dim3(threads), 0, st, L, w2, width, layer_max, n_tiles);
     return hipGetLastError();
 }
 
 // FP64 arithmetic up to M = 2048, FP32 for M = 4096.
-template <class R, class XT, class OutT, int CC, int NIT, int NF>
+template <class R, class XT, class OutT, int CC, int NIT>
 static hipError_t run_fft_t(const TransformLaunch &L, double w2, uint32_t *layer_max, hipStream_t st) {
     if constexpr (sizeof(R) == 4) {
-        if (L.M == 4096) return run_fft_m<R, XT, OutT, 4096, CC, NIT, NF>(L, w2, layer_max, st);
+        if (L.M == 4096) return run_fft_m<R, XT, OutT, 4096, CC, NIT>(L, w2, layer_max, st);
     } else {
         switch (L.M) {
-            case 64: return run_fft_m<R, XT, OutT, 64, CC, NIT, NF>(L, w2, layer_max, st);
-            case 128: return run_fft_m<R, XT, OutT, 128, CC, NIT, NF>(L, w2, layer_max, st);
-            case 256: return run_fft_m<R, XT, OutT, 256, CC, NIT, NF>(L, w2, layer_max, st);
-            case 512: return run_fft_m<R, XT, OutT, 512, CC, NIT, NF>(L, w2, layer_max, st);
-            case 1024: return run_fft_m<R, XT, OutT, 1024, CC, NIT, NF>(L, w2, layer_max, st);
-            case 2048: return run_fft_m<R, XT, OutT, 2048, CC, NIT, NF>(L, w2, layer_max, st);
+            case 64: return run_fft_m<R, XT, OutT, 64, CC, NIT>(L, w2, layer_max, st);
+            case 128: return run_fft_m<R, XT, OutT, 128, CC, NIT>(L, w2, layer_max, st);
+            case 256: return run_fft_m<R, XT, OutT, 256, CC, NIT>(L, w2, layer_max, st);
+            case 512: return run_fft_m<R, XT, OutT, 512, CC, NIT>(L, w2, layer_max, st);
+            case 1024: return run_fft_m<R, XT, OutT, 1024, CC, NIT>(L, w2, layer_max, st);
+            case 2048: return run_fft_m<R, XT, OutT, 2048, CC, NIT>(L, w2, layer_max, st);
         }
     }
     return hipErrorInvalidValue;
 }
 
-// Channel-interleaved cells take all their channels in one block, the other layouts one channel.  NIT: transforms
-// held until the store, chosen for runs of at least 64 bytes per frequency layer.  FP64 transforms (M <= 2048) run
-// 256 threads, FP32 ones (M = 4096) 512.  The 16-byte stores of FP32 A+E cells need a store aligned to them; another one
-// takes the one-channel form, which writes any layout 8 or 16 bytes at a time.
+// Which transforms a block runs one after the other, NIT of them, until its store.  Blocks of one transform (1, 1) fill the
+// chip where a set is short: it is done when its longest block is.  Above that the cells of two channels take both in one
+// block, for whole cells per store (M = 2048, FP32 store, 350 tranches: 15.0 us a call with one transform a block, 15.9
+// with a cell's two; 3,083: 57.6 against 46.0; M = 512, FP64 store, 500 tranches: 13.1 against 15.3).  One channel, and the
+// layouts that keep channels apart, stay with one transform (one channel, M = 2048, 3,083 tranches, FP32: 32 us against 43
+// with two pairs), as do FP32 cells of three channels (85 against 95).  From more than 1024 blocks on (768 run at once)
+// three channels' FP64 cells and 16-bit stores take a cell's channels, or two pairs of a channel: the writes of a cell join,
+// and a block sends half the maxima (M = 2048, C = 3, FP64: 500 tranches, 750 blocks, 24 us against 26; 3,083: 139 against
+// 117; 16 bits of one channel, 1,500: 38 against 39; 6,144: 97 against 89).  Not for M = 4096, whose blocks of 512 threads
+// come one or two to a CU (16 bits of one channel, 3,083 tranches: 90 against 112).
+// The 16-byte stores of FP32 A+E cells need a store aligned to them; another one takes the one-channel form, which writes
+// any layout 8 or 16 bytes at a time.
 template <class R, class XT, class OutT>
 static hipError_t run_fft(const TransformLaunch &L, double w2, uint32_t *layer_max, hipStream_t st) {
-    constexpr int D = sizeof(OutT) / 4;
-    if (L.out_layout != 2 || L.C == 1 || reinterpret_cast<uintptr_t>(L.pix) % 16 != 0)
-        return run_fft_t<R, XT, OutT, 1, 2, 2 / D>(L, w2, layer_max, st);
-    if (L.C == 2) return run_fft_t<R, XT, OutT, 2, 2, 2 / D>(L, w2, layer_max, st);
-    return run_fft_t<R, XT, OutT, 3, 3, 2 / D>(L, w2, layer_max, st);
+    const bool cells = L.out_layout == 2 && L.C > 1 && reinterpret_cast<uintptr_t>(L.pix) % 16 == 0;
+    const int per = 2 * (sizeof(R) == 8 ? 2048 / L.M : 1);  // tranches of a block of one transform per group
+    const int64_t blocks = (int64_t)L.C * ((L.Nt + per - 1) / per);
+    if (cells && L.C == 2 && blocks > (sizeof(R) == 8 ? 512 : 256)) return run_fft_t<R, XT, OutT, 2, 2>(L, w2, layer_max, st);
+    if constexpr (sizeof(R) == 8) {
+        const bool many = blocks > 1024;
+        if (many && cells && L.C == 3 && (layer_max || sizeof(OutT) == 8))
+            return run_fft_t<R, XT, OutT, 3, 3>(L, w2, layer_max, st);
+        if constexpr (sizeof(OutT) == 4)
+            if (many && layer_max) return run_fft_t<R, XT, OutT, 1, 2>(L, w2, layer_max, st);
+    }
+    return run_fft_t<R, XT, OutT, 1, 1>(L, w2, layer_max, st);
 }
 
 template <class Q>

@@ -132,6 +132,40 @@ def test_layer_scale_is_the_maximum_of_stored_pixels(C, M, Nt, layout):
     assert np.array_equal(got.cpu().numpy(), np.where(top > 0, top / np.float32(32767.0), np.float32(1.0)))
 
 
+@pytest.mark.parametrize("C, M, Nt, dtype, layout", [
+    (2, 2048, 515, "f32", "layer_ci"), (2, 64, 16_453, "f64", "layer_ci"), (2, 256, 4_117, "i16", "layer_ci"),
+    (2, 4096, 259, "f32", "layer_ci"), (3, 2048, 685, "f64", "layer_ci"), (3, 64, 21_895, "i16", "layer_ci"),
+    (1, 512, 8_205, "i16", "layer"), (2, 1024, 2_053, "i16", "tranche"), (1, 2048, 2_055, "i16", "layer_ci")])
+def test_transform_of_many_tranches_equals_its_pieces(C, M, Nt, dtype, layout):
+    """Sets just above the sizes from which a block does several transforms, with a remainder, against the same tranches
+    in pieces below them (an even number, so that the same tranches are paired): the same bits.  A 16-bit store's scale is
+    the largest component over its grid, its pixels within half a step and two float roundings of at most 32767."""
+    tfsc = lib()
+    note(f"transform of many tranches C={C} M={M} Nt={Nt} {dtype} {layout}")
+    f = "f32" if dtype == "i16" else dtype
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    x = torch.randn((C, Nt, M), generator=gen, device="cuda", dtype=torch.float64 if dtype == "f64" else torch.float32)
+
+    def run(a, b, d):
+        n = b - a
+        return tfsc.transform(tfsc.GridSpec(C, M, n, 5.0, 0.1), x[:, a:b].contiguous(), dev(np.ones(M // 2 + 1)),
+                              dev(np.ones(n)), dev(np.ones(n, np.uint8)), dtype=d, layout=layout)
+
+    at = {"layer": 2, "tranche": 1, "layer_ci": 1}[layout]
+    step = 2 * (2048 // M or 1) * 20
+    want = torch.cat([run(a, min(a + step, Nt), f).pix for a in range(0, Nt, step)], dim=at)
+    assert torch.equal(run(0, Nt, f).pix, want)
+    if dtype == "i16":
+        got = run(0, Nt, "i16")
+        over = {"layer": (2, 3), "tranche": (1, 3), "layer_ci": (1, 3)}[layout]
+        top = want.abs().amax(dim=over)
+        scale = (top.T if layout == "layer_ci" else top).cpu().numpy() / np.float32(32767.0)
+        assert np.array_equal(got.layer_scale.cpu().numpy(), scale)
+        top = {"layer": lambda v: v[:, :, None, None], "tranche": lambda v: v[:, None, :, None],
+               "layer_ci": lambda v: v[:, None, :, None]}[layout](top.double())
+        assert float((got.pix.double() - want.double() * (32767.0 / top)).abs().max()) <= 0.5 + 2.0 * 32767.0 * 2.0 ** -24
+
+
 def _bank(tfsc, n, seed):
     b = ti.random_bank(n, seed, mc_range=(5.0, 100.0), f0_range=(0.004, 0.08), eta=None, stream=62)
     if n > 20:
