@@ -220,7 +220,14 @@ enum {
     TFSC_FLAG_ALL_EXCLUDED = 16 /* every active tranche excluded (w_m = 0)   */
 };
 
-enum { TFSC_WS_LAYOUT = 0, TFSC_WS_STATISTIC = 1, TFSC_WS_VJP = 2, TFSC_WS_TRANSFORM = 3, TFSC_WS_ORDER = 4 };
+enum {
+    TFSC_WS_LAYOUT = 0,
+    TFSC_WS_STATISTIC = 1,
+    TFSC_WS_VJP = 2,
+    TFSC_WS_TRANSFORM = 3,
+    TFSC_WS_ORDER = 4,
+    TFSC_WS_WHOLE = 5 /* TFSC_WS_STATISTIC and TFSC_WS_VJP without their optional scratch */
+};
 
 int tfsc_abi_version(void);
 const char *tfsc_status_string(int status);
@@ -230,11 +237,17 @@ const char *tfsc_status_string(int status);
  * initialised; calls sharing one workspace must not overlap in time.  The
  * statistic and VJP figures include 8 bytes per template for a bank given
  * in ln Mc (the calls form exp(ln Mc) there once); an mc bank needs only
- * the geometry tables and 256 bytes, and the calls check that need.  The
- * statistic's figure also holds optional scratch (at most 128 MiB) with
- * which tfsc_bank_statistic shares out the tranches of small and medium
- * banks over more waves; with a workspace that lacks it, it takes whole
- * templates: the same results, bit for bit, later.                         */
+ * the geometry tables and 256 bytes, and the calls check that need.
+ * TFSC_WS_STATISTIC and TFSC_WS_VJP also hold optional scratch (at most 128
+ * MiB each), with which tfsc_bank_statistic in the WAVE schedule (paper's
+ * Fresnel forms, equal arms) and tfsc_statistic_vjp share out the tranches
+ * of small and medium banks over more waves.  With a workspace that lacks
+ * it they take whole templates, later: the statistic with the same results,
+ * bit for bit, the VJP with another order of its FP64 sums over the
+ * tranches (and FP64 asymptotic bins one by one instead of through their
+ * moments; equal to some 1e-14 of the largest gradient).  No other call uses
+ * that scratch: TFSC_WS_WHOLE is the size without it.  With opt NULL the
+ * figures are enough for either precision.                                 */
 size_t tfsc_workspace_bytes(const tfsc_grid *grid, int64_t n_templates, const tfsc_options *opt, int which);
 
 /* Data -> TF pixels (paper Sec. "Implementation details": each tranche is
@@ -325,7 +338,7 @@ tfsc_status tfsc_bank_statistic(const tfsc_grid *grid, const tfsc_pixels *pix, c
  * seg_zn (the VJP takes one realisation).  Sums are
  * formed per bin rather than through the single-realisation kernel's
  * factored asymptotic sums, so the two agree to rounding, not bit for bit.
- * Needs TFSC_WS_STATISTIC workspace.                                       */
+ * Needs TFSC_WS_WHOLE workspace.                                           */
 tfsc_status tfsc_bank_statistic_multi(const tfsc_grid *grid, const tfsc_pixels *pix, int32_t n_real,
                                       int64_t real_stride, int32_t group, const tfsc_bank *bank,
                                       const tfsc_segments *seg, const tfsc_options *opt, int64_t seg_stride,
@@ -463,7 +476,7 @@ tfsc_status tfsc_tile_max(const double *stat, const int32_t *tile, int64_t n, in
  * LAYER_MAJOR or LAYER_MAJOR_CI, F64 pixels with F64 precision or F32 with
  * F32 (else TFSC_ERR_DTYPE), no rho, the paper's Fresnel forms (else
  * TFSC_ERR_UNSUPPORTED).  h = {2}, a = 1 is tfsc_bank_statistic's template.
- * Needs TFSC_WS_STATISTIC workspace.                                       */
+ * Needs TFSC_WS_WHOLE workspace.                                           */
 #define TFSC_MAX_HARMONICS 4
 tfsc_status tfsc_bank_statistic_harmonics(const tfsc_grid *grid, const tfsc_pixels *pix, const tfsc_bank *bank,
                                           const tfsc_segments *seg, const tfsc_options *opt, int32_t n_harm,

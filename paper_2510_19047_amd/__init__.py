@@ -253,7 +253,8 @@ def bank_statistic(grid: GridSpec, pixels: PixelStore, bank: BankTensors, seg: S
                          torch.empty(bank.n, dtype=torch.int32, device=dev) if want_active else None)
     g = grid.c()
     opt = _options(precision, schedule, block_waves, groups_per_cu, order, fresnel, tune_key)
-    nb = L.tfsc_workspace_bytes(ctypes.byref(g), bank.n, ctypes.byref(opt), _lib.WS_STATISTIC)
+    nb = L.tfsc_workspace_bytes(ctypes.byref(g), bank.n, ctypes.byref(opt),
+                                _lib.WS_STATISTIC if pixels.links is None else _lib.WS_WHOLE)
     if ws is None or ws.numel() < nb:
         ws = _ws(nb, dev)
     pc, bc, sc = pixels.c(), bank.c(), seg.c()
@@ -311,7 +312,7 @@ def bank_statistic_harmonics(grid: GridSpec, pixels: PixelStore, bank: BankTenso
                          torch.empty(bank.n, dtype=torch.int32, device=dev) if want_active else None)
     g = grid.c()
     opt = _options(precision, "wave", block_waves, groups_per_cu, order)
-    nb = L.tfsc_workspace_bytes(ctypes.byref(g), bank.n, ctypes.byref(opt), _lib.WS_STATISTIC)
+    nb = L.tfsc_workspace_bytes(ctypes.byref(g), bank.n, ctypes.byref(opt), _lib.WS_WHOLE)
     ws = _ws(nb, dev)
     harr = (ctypes.c_int32 * max(H, 1))(*hs)
     pc, bc, sc = pixels.c(), bank.c(), seg.c()
@@ -353,7 +354,7 @@ def tune_statistic(grid: GridSpec, pixels: PixelStore, bank: BankTensors, seg: S
                      torch.empty(bank.n, dtype=torch.int32, device=dev))
     g = grid.c()
     opt = _options(precision, "wave", 0, 0, order)
-    nb = L.tfsc_workspace_bytes(ctypes.byref(g), bank.n, ctypes.byref(opt), _lib.WS_STATISTIC)
+    nb = L.tfsc_workspace_bytes(ctypes.byref(g), bank.n, ctypes.byref(opt), _lib.WS_WHOLE)
     ws = _ws(nb, dev)
     pc, bc, sc = pixels.c(), bank.c(), seg.c()
     bw, gpc = ctypes.c_int32(0), ctypes.c_int32(0)
@@ -415,7 +416,7 @@ def bank_statistic_multi(grid: GridSpec, stores: list, bank: BankTensors, seg: S
                           torch.empty(bank.n, dtype=torch.int32, device=dev) if want_active else None)
     g = grid.c()
     opt = _options(precision, "wave", block_waves, groups_per_cu, order)
-    nb = L.tfsc_workspace_bytes(ctypes.byref(g), bank.n, ctypes.byref(opt), _lib.WS_STATISTIC)
+    nb = L.tfsc_workspace_bytes(ctypes.byref(g), bank.n, ctypes.byref(opt), _lib.WS_WHOLE)
     if ws is None or ws.numel() < nb:
         ws = _ws(nb, dev)
     pc, bc, sc = stores[0].c(), bank.c(), seg.c()
@@ -475,7 +476,7 @@ def bank_statistic_interleaved(grid: GridSpec, store: PixelStore, n_real: int, b
                           torch.empty(bank.n, dtype=torch.int32, device=dev) if want_active else None)
     g = grid.c()
     opt = _options("f32", "wave", block_waves, groups_per_cu, order)
-    nb = L.tfsc_workspace_bytes(ctypes.byref(g), bank.n, ctypes.byref(opt), _lib.WS_STATISTIC)
+    nb = L.tfsc_workspace_bytes(ctypes.byref(g), bank.n, ctypes.byref(opt), _lib.WS_WHOLE)
     if ws is None or ws.numel() < nb:
         ws = _ws(nb, dev)
     pc, bc, sc = store.c(), bank.c(), seg.c()

@@ -18,7 +18,7 @@ NOALLOC_MAX_TRANCHES = 16384
 F64, F32, BF16, F16, I16 = 0, 1, 2, 3, 4
 LAYER_MAJOR, TRANCHE_MAJOR, LAYER_MAJOR_CI = 0, 1, 2
 SCHED_THREAD, SCHED_WAVE = 0, 1
-WS_LAYOUT, WS_STATISTIC, WS_VJP, WS_TRANSFORM, WS_ORDER = 0, 1, 2, 3, 4
+WS_LAYOUT, WS_STATISTIC, WS_VJP, WS_TRANSFORM, WS_ORDER, WS_WHOLE = 0, 1, 2, 3, 4, 5
 FLAG_INVALID, FLAG_EMPTY, FLAG_BAND_END, FLAG_MERGE_END, FLAG_ALL_EXCLUDED = 1, 2, 4, 8, 16
 
 

@@ -189,16 +189,27 @@ void use_vjp_split(const tfsc_grid *g, tfsc::StatLaunch &L, void *ws, size_t ws_
     L.split = s;
 }
 
-size_t ws_bytes_for(const tfsc_grid *g, int64_t n, int which, size_t elem = sizeof(double)) {
+// opt NULL: enough for either precision.  The THREAD schedule and the accurate Fresnel mode do not split.
+size_t ws_bytes_for(const tfsc_grid *g, int64_t n, int which, const tfsc_options *opt = nullptr) {
+    const size_t whole = stat_ws_bytes(g, n, true);
+    auto either = [&](auto &&bytes) {
+        const size_t b64 = opt && opt->precision == TFSC_F32 ? 0 : bytes(sizeof(double));
+        const size_t b32 = opt && opt->precision != TFSC_F32 ? 0 : bytes(sizeof(float));
+        return b64 > b32 ? b64 : b32;
+    };
     switch (which) {
         case TFSC_WS_LAYOUT:
             return align_up(sizeof(int64_t) * (size_t)((n + 255) / 256 + 1));
+        case TFSC_WS_WHOLE:
+            return whole;
         case TFSC_WS_STATISTIC:
-            return stat_ws_bytes(g, n, true) + split_bytes(n, split_for(g, n, elem), elem);
-        case TFSC_WS_VJP: {
-            const size_t b = vjp_split_bytes(n, vjp_split_for(g, n, elem));
-            return stat_ws_bytes(g, n, true) + (b > kSplitMost ? 0 : b);
-        }
+            if (opt && (opt->schedule != TFSC_SCHED_WAVE || opt->fresnel != TFSC_FRESNEL_PAPER)) return whole;
+            return whole + either([&](size_t elem) { return split_bytes(n, split_for(g, n, elem), elem); });
+        case TFSC_WS_VJP:
+            return whole + either([&](size_t elem) {
+                       const size_t b = vjp_split_bytes(n, vjp_split_for(g, n, elem));
+                       return b > kSplitMost ? 0 : b;
+                   });
         case TFSC_WS_ORDER:
         {
             const size_t nb = (size_t)(g->tranche_len / 2 + 1) * tfsc::kOrderMcClasses + 1;
@@ -338,7 +349,7 @@ const char *tfsc_status_string(int s) {
 
 size_t tfsc_workspace_bytes(const tfsc_grid *grid, int64_t n_templates, const tfsc_options *opt, int which) {
     if (check_grid(grid) != TFSC_OK || n_templates < 0) return 0;
-    return ws_bytes_for(grid, n_templates, which, opt && opt->precision == TFSC_F32 ? sizeof(float) : sizeof(double));
+    return ws_bytes_for(grid, n_templates, which, opt);
 }
 
 tfsc_status tfsc_segment_layout(const tfsc_grid *grid, const tfsc_bank *bank, tfsc_segments *seg, void *ws,

@@ -258,3 +258,26 @@ def test_tdi_generation_argument_errors(L):
     assert stat(_lib.Pixels(1, 2, p, None, p, p, None, None, p, 3)) == 1
     assert stat(_lib.Pixels(1, 2, p, None, p, p, None, None, p, -1)) == 1
     assert stat(_lib.Pixels(1, 2, p, None, p, p, None, None, None, 2)) == 5
+
+
+def test_workspace_without_the_optional_scratch(L):
+    """The scratch of split templates is asked for where a call can use it, and only there; without options it is
+    enough for either precision."""
+    from paper_2510_19047_amd import _lib
+    g = _grid()
+
+    def nb(n, which, **kw):
+        opt = _lib.Options(kw.get("precision", _lib.F32), kw.get("schedule", _lib.SCHED_WAVE), 0, 0, None,
+                           kw.get("fresnel", _lib.FRESNEL_PAPER), None)
+        return L.tfsc_workspace_bytes(ctypes.byref(g), n, ctypes.byref(opt) if kw.get("opt", True) else None, which)
+
+    for n in (20, 4099, 60_000):
+        whole = nb(n, _lib.WS_WHOLE)
+        assert whole < 8 * n + 256 * 8 * 6144
+        assert whole < nb(n, _lib.WS_STATISTIC) <= whole + (128 << 20)
+        assert nb(n, _lib.WS_STATISTIC, schedule=_lib.SCHED_THREAD) == whole
+        assert nb(n, _lib.WS_STATISTIC, fresnel=_lib.FRESNEL_ACCURATE) == whole
+        for which in (_lib.WS_STATISTIC, _lib.WS_VJP):
+            each = [nb(n, which, precision=p) for p in (_lib.F64, _lib.F32)]
+            assert nb(n, which, opt=False) == max(each)
+    assert nb(60_000, _lib.WS_STATISTIC, precision=_lib.F64) == nb(60_000, _lib.WS_WHOLE)  # would take more than 128 MiB
