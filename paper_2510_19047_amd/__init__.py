@@ -242,7 +242,8 @@ def bank_statistic(grid: GridSpec, pixels: PixelStore, bank: BankTensors, seg: S
                    ws: torch.Tensor | None = None, want_active: bool = False, fresnel: str = "paper",
                    tune_key: str | None = None) -> StatResult:
     """tfsc_bank_statistic: Upsilon, per-segment terms and flags for every template (``fresnel``: "paper" for the
-    paper's Fresnel forms, "accurate" for the Fresnel integrals)."""
+    paper's Fresnel forms, "accurate" for the Fresnel integrals).  ``ws`` is the workspace if it holds the call's
+    tables; the optional scratch of split templates behind them is used as far as ``ws`` has it."""
     L = lib()
     dev = bank.device
     if out is None:
@@ -253,10 +254,9 @@ def bank_statistic(grid: GridSpec, pixels: PixelStore, bank: BankTensors, seg: S
                          torch.empty(bank.n, dtype=torch.int32, device=dev) if want_active else None)
     g = grid.c()
     opt = _options(precision, schedule, block_waves, groups_per_cu, order, fresnel, tune_key)
-    nb = L.tfsc_workspace_bytes(ctypes.byref(g), bank.n, ctypes.byref(opt),
-                                _lib.WS_STATISTIC if pixels.links is None else _lib.WS_WHOLE)
-    if ws is None or ws.numel() < nb:
-        ws = _ws(nb, dev)
+    if ws is None or ws.numel() < L.tfsc_workspace_bytes(ctypes.byref(g), bank.n, ctypes.byref(opt), _lib.WS_WHOLE):
+        ws = _ws(L.tfsc_workspace_bytes(ctypes.byref(g), bank.n, ctypes.byref(opt),
+                                        _lib.WS_STATISTIC if pixels.links is None else _lib.WS_WHOLE), dev)
     pc, bc, sc = pixels.c(), bank.c(), seg.c()
     st = L.tfsc_bank_statistic(ctypes.byref(g), ctypes.byref(pc), ctypes.byref(bc), ctypes.byref(sc),
                                ctypes.byref(opt), _ptr(out.seg_terms), _ptr(out.stat), _ptr(out.seg_zn),

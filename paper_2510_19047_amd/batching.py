@@ -21,7 +21,7 @@ import torch
 
 import ctypes
 
-from . import (BankTensors, GridSpec, PixelStore, SegmentLayout, StatResult, TfscError, _lib, bank_statistic,
+from . import (BankTensors, GridSpec, PixelStore, SegmentLayout, StatResult, TfscError, _lib, _options, bank_statistic,
                bank_statistic_interleaved, bank_statistic_multi, interleave_store, interleaved_store, lib,
                realisation_stores, transform, tune_statistic)
 
@@ -93,14 +93,16 @@ class RealisationGraph:
         self.multi, self.group, self.interleave = multi, group, interleave
         R = xs.shape[0]
         dev = bank.device
+        if interleave and (store not in ("f32", "i16") or layout != "layer_ci" or precision != "f32" or R % interleave):
+            raise TfscError("interleaved realisations take f32 or i16 channel-interleaved stores, R a multiple of NR")
         L = lib()
         g = grid.c()
-        nb = L.tfsc_workspace_bytes(ctypes.byref(g), bank.n, None, _lib.WS_STATISTIC)
+        # the passes over several realisations take whole templates
+        opt = _options(precision, "wave", order=order, **self.shape)
+        nb = L.tfsc_workspace_bytes(ctypes.byref(g), bank.n, ctypes.byref(opt),
+                                    _lib.WS_WHOLE if multi or interleave else _lib.WS_STATISTIC)
         self.ws = torch.empty(max(nb, 1), dtype=torch.uint8, device=dev)
         if interleave:
-            if store not in ("f32", "i16") or layout != "layer_ci" or precision != "f32" or R % interleave:
-                raise TfscError("interleaved realisations take f32 or i16 channel-interleaved stores, R a "
-                                "multiple of NR")
             self.staging = transform(grid, xs[0], psd0, mu, keep, dtype=store, layout="layer_ci")
             self.groups = []
             for q in range(R // interleave):
