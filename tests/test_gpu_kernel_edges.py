@@ -1,4 +1,6 @@
 """Edges of the kernels' tiles, remainders and dispatch rules, against numpy or the oracle."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -261,6 +263,76 @@ def test_vjp_units_equal_whole_templates(C, layout, dtype, precision):
     a, b = out[0][:5003], out[1]
     assert torch.isfinite(b).all()
     assert float(((a - b).abs() / a.abs().amax(dim=0)).max()) < 1e-9
+
+
+def _noise_store(tfsc, grid, C, M, Nt, dtype, layout, rho, gen):
+    """Unit-variance noise pixels, a tenth of the tranches excluded; a 16-bit store through the transform."""
+    K = M // 2 + 1
+    w = (torch.rand(Nt, generator=gen, device="cuda") > 0.1).to(torch.float64)
+    if dtype == "i16":
+        x = torch.randn((C, M * Nt), generator=gen, device="cuda")
+        store = tfsc.transform(grid, x, dev(np.ones(K)), dev(np.ones(Nt)), w.to(torch.uint8), dtype="i16", layout=layout)
+    else:
+        z = torch.view_as_complex(torch.randn((C, K, Nt, 2), generator=gen, device="cuda"))
+        store = tfsc.PixelStore.from_complex(z, dev(np.ones(K)), w, dtype, layout)
+    if rho:
+        store.rho = 0.5 + torch.rand((K, Nt), generator=gen, device="cuda")
+    return store
+
+
+def _whole(tfsc, grid, n, precision):
+    """A workspace without the scratch of split templates."""
+    g, opt = grid.c(), tfsc._options(precision)
+    nb = tfsc.lib().tfsc_workspace_bytes(ctypes.byref(g), n, ctypes.byref(opt), tfsc._lib.WS_WHOLE)
+    return torch.empty(nb, dtype=torch.uint8, device="cuda")
+
+
+@pytest.mark.parametrize("C, layout, dtype, precision, rho", [
+    (2, "layer_ci", "f32", "f32", False), (2, "layer_ci", "f32", "f32", True), (2, "layer_ci", "i16", "f32", False),
+    (1, "layer", "f32", "f32", False), (3, "layer_ci", "f32", "f32", False), (3, "layer", "i16", "f32", False),
+    (2, "layer", "f64", "f64", True), (1, "layer_ci", "f32", "f64", False)])
+@pytest.mark.parametrize("n, nseg", [(1, 7), (300, 0), (2000, 3), (6000, 40), (20_000, 0)])
+def test_units_of_several_chunks_equal_whole_templates(C, layout, dtype, precision, rho, n, nseg):
+    """35 chunks of tranches in units of 1, 2, 6 and 16 (on 256 CUs; the last unit is shorter) against whole templates,
+    bit for bit: segments inside a unit, over several units and their chunks, tracks that end in any of them."""
+    tfsc = lib()
+    M, Nt = 64, 2200
+    grid = tfsc.GridSpec(C, M, Nt, 5.0, 0.1)
+    store = _noise_store(tfsc, grid, C, M, Nt, dtype, layout, rho, torch.Generator(device="cuda").manual_seed(n + C))
+    bank = _bank(tfsc, n, 31)
+    seg = tfsc.segment_layout(grid, bank, nseg)
+    note(f"units of several chunks: C={C} {layout} {dtype}/{precision} rho={rho} n={n} nseg={nseg}")
+    kw = dict(precision=precision, want_zn=True, want_active=True)
+    a = tfsc.bank_statistic(grid, store, bank, seg, ws=_whole(tfsc, grid, n, precision), **kw)
+    for order in (None, tfsc.processing_order(grid, bank)):
+        _all_equal(tfsc.bank_statistic(grid, store, bank, seg, order=order, **kw), a)
+
+
+@pytest.mark.parametrize("C, layout, dtype, rho", [(2, "layer_ci", "f32", False), (3, "tranche", "i16", False),
+                                                   (1, "layer", "f64", True)])
+@pytest.mark.parametrize("precision", ["f32", "f64"])
+@pytest.mark.parametrize("n", [1, 30, 1500])
+def test_vjp_units_of_several_chunks_equal_whole_templates(C, layout, dtype, rho, precision, n):
+    """The VJP in units of 1 and of 3 (FP32) and 6 (FP64) of the 35 chunks against whole templates: equal but for the order of the
+    FP64 sum over the tranches, at most 2200 terms of at most 1e3 times the largest gradient, so below
+    2200 * 1.1e-16 * 1e3 = 2.4e-10 of it; 1e-9 is asked for."""
+    tfsc = lib()
+    M, Nt = 64, 2200
+    grid = tfsc.GridSpec(C, M, Nt, 5.0, 0.1)
+    store = _noise_store(tfsc, grid, C, M, Nt, dtype, layout, rho, torch.Generator(device="cuda").manual_seed(n + C))
+    bank = _bank(tfsc, n, 37)
+    seg = tfsc.segment_layout(grid, bank, 5)
+    zn = torch.rand((5 * n, 3), generator=torch.Generator(device="cuda").manual_seed(3), device="cuda", dtype=torch.float64)
+    note(f"VJP units of several chunks: C={C} {layout} {dtype} rho={rho} {precision} n={n}")
+    ones = torch.ones(n, dtype=torch.float64, device="cuda")
+    b = tfsc.statistic_vjp(grid, store, bank, seg, zn, g_stat=ones, precision=precision)
+    a, ws = torch.empty_like(b), _whole(tfsc, grid, n, precision)
+    g, opt, pc, bc, sc = grid.c(), tfsc._options(precision), store.c(), bank.c(), seg.c()
+    st = tfsc.lib().tfsc_statistic_vjp(ctypes.byref(g), ctypes.byref(pc), ctypes.byref(bc), ctypes.byref(sc),
+                                       ctypes.byref(opt), zn.data_ptr(), ones.data_ptr(), None, a.data_ptr(),
+                                       ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+    assert st == 0 and torch.isfinite(b).all()
+    assert ((a - b).abs() <= 1e-9 * a.abs().amax(dim=0)).all()
 
 
 @pytest.mark.parametrize("n, n_real, C", [(1, 2, 1), (515, 2, 2), (2049, 4, 1)])
