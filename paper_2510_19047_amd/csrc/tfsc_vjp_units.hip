@@ -4,6 +4,8 @@
 // block), and the FP32 results carry it: a change here is compared with the results before it.
 #include "tfsc_vjp_common.hpp"
 
+#include <type_traits>
+
 namespace tfsc {
 
 // ------------------------------------------------------------------ bin sums
@@ -354,8 +356,12 @@ __global__ __launch_bounds__(256, sizeof(R) == 4 ? 2 : 1) void k_vjp_units(VjpAr
                                         dr *= sc;
                                         di *= sc;
                                     }
-                                    // conj(D) x
-                                    S1r[c] += dr * hr + di * hi;
+                                    // conj(D) x.  Of an I16 store k_vjp_wave's text rounds the first product and fuses the
+                                    // second, here it would be the other way round: written out, for the same results.
+                                    if constexpr (std::is_same<PixT, int16_t>::value)
+                                        S1r[c] += fma(di, hi, dr * hr);
+                                    else
+                                        S1r[c] += dr * hr + di * hi;
                                     S1i[c] += dr * hi - di * hr;
 #pragma unroll
                                     for (int p = 0; p < 2; ++p) {
