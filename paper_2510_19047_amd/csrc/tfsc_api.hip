@@ -180,6 +180,9 @@ size_t vjp_split_bytes(int64_t n, const tfsc::SplitWs &s) {
 }
 
 void use_vjp_split(const tfsc_grid *g, tfsc::StatLaunch &L, void *ws, size_t ws_bytes, bool log_mc) {
+    // FP32 of 16-bit stores: up to eight templates a wave, where the loads' latency still counts.  Two-year grid, A+E, I16,
+    // whole against split, ms: 10,000 templates 9.12 / 8.82; 20,000 16.9 / 17.3; 40,000 32.7 / 34.1.
+    if (L.precision == 1 && is_16bit(L.pix_dtype) && L.n > (int64_t)device_cus() * 8 * 8) return;
     tfsc::SplitWs s = vjp_split_for(g, L.n, L.precision == 0 ? sizeof(double) : sizeof(float));
     const size_t base = stat_ws_bytes(g, L.n, log_mc), need = vjp_split_bytes(L.n, s);
     if (!s.units || need > kSplitMost || ws_bytes < base + need) return;
