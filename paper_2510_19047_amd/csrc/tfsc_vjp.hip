@@ -275,11 +275,11 @@ hipError_t launch_vjp(const VjpLaunch &V, hipStream_t st) {
     a.g_stat = V.g_stat;
     a.g_seg = V.g_seg;
     a.g_params = V.g_params;
-    a.units = L.split.units ? L.split.units : 1;
-    a.chunks = L.split.units ? L.split.chunks : (L.Nt + 63) / 64;
-    a.rec = L.split.units ? L.split.rec : nullptr;
+    a.units = L.split.units;
+    a.chunks = L.split.chunks;
+    a.rec = L.split.rec;
     a.part = reinterpret_cast<double *>(L.split.head);
-    if (a.units > 1) return launch_vjp_units(a, L.precision, L.C, L.pix_dtype, kRunWaves, st);
+    if (a.units) return launch_vjp_units(a, L.precision, L.C, L.pix_dtype, kRunWaves, st);
     return L.precision == 1 ? dispatch_vjp_c<float>(a, L.layout, L.counter, L.C, L.pix_dtype, L.n_groups, L.block_waves, st)
                             : dispatch_vjp_c<double>(a, L.layout, L.counter, L.C, L.pix_dtype, L.n_groups, L.block_waves, st);
 }

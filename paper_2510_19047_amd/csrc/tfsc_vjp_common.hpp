@@ -549,10 +549,10 @@ struct VjpArgs {
     const int64_t *seg_offset;
     const double *seg_zn, *g_stat, *g_seg;
     double *g_params;
-    // each wave takes one unit of `chunks` chunks of a template (units per template: 1 = whole templates)
+    // split templates (k_vjp_units): each wave takes one unit of `chunks` chunks; units per template (0: whole templates)
     int units, chunks;
-    const double *rec;  // template records (k_prepare), or NULL
-    double *part;       // [n][units][5] gradients of the units, if units > 1
+    const double *rec;  // template records (k_prepare)
+    double *part;       // [n][units][5] gradients of the units
 };
 
 hipError_t launch_vjp_units(const VjpArgs &a, int precision, int C, int dtype, int block_waves, hipStream_t st);

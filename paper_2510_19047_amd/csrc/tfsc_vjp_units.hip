@@ -197,12 +197,7 @@ __global__ __launch_bounds__(256, sizeof(R) == 4 ? 2 : 1) void k_vjp_units(VjpAr
             const int64_t off = a.seg_offset[i];
             const double gs = a.g_stat ? a.g_stat[i] : 0.0;
             Track T;
-            if (a.rec) {
-                load_track(a.rec + i * kRecDoubles, lane, T);
-            } else {
-                track_init(T, mci, a.eta[i], a.f0[i]);
-                wave_uniform(T);
-            }
+            load_track(a.rec + i * kRecDoubles, lane, T);
             TrackTan TT = track_tangents(T, a.f0[i]);
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
@@ -450,7 +445,7 @@ __global__ __launch_bounds__(256, sizeof(R) == 4 ? 2 : 1) void k_vjp_units(VjpAr
         for (int p = 0; p < 5; ++p) gr[p] = dpp_sum_f64(gr[p]);
         if (lane == 0) {
             // ln Mc, f0, cos theta, phi, psi
-            double *o = a.units > 1 ? a.part + 5 * (i * a.units + unit) : a.g_params + 5 * i;
+            double *o = a.part + 5 * (i * a.units + unit);
 #pragma unroll
             for (int p = 0; p < 5; ++p) o[p] = gr[p];
         }
