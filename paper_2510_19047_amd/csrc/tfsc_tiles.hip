@@ -7,11 +7,12 @@
 // kernel, so the sequence can be captured into a HIP graph.
 //
 // What bounds it: reading stat and tile (12 bytes per template) twice, the second time from the Infinity
-// Cache.  A bank has far more templates than tiles, so one global atomic per template serialises on the few
-// addresses (4M templates on 64 tiles: 4122 us, about 1 ns per atomic).  The maximum pass therefore reduces in
-// LDS first and a running maximum is raised only by values above it (a few times per tile and block), and the
-// block sends its tiles' maxima on with one comparison each.  4M templates, 64 tiles: 23 us for
-// the maximum pass and 11 us for the index pass (4.4 TB/s).
+// Cache.  With many templates per tile, one global atomic per template serialises on the few addresses (4M
+// templates on 64 tiles: 4122 us, about 1 ns per atomic).  The maximum pass then reduces in LDS first, where a
+// running maximum is raised only by values above it (a few times per tile and block), and the block sends its
+// tiles' maxima on with one comparison each: 4M templates, 64 tiles, 23 us for the maximum pass and 11 us for the
+// index pass (4.4 TB/s).  With few templates per tile the atomics hardly meet and the blocks' tables would be the
+// larger part: each template sends its own (launch_tile_max has the rule).
 #include "tfsc_kernels.hpp"
 
 #include <hip/hip_runtime.h>
@@ -23,9 +24,8 @@ namespace {
 
 constexpr unsigned long long kNoIndex = ~0ull;  // int64 -1: the tile holds no template
 
-// Tiles whose running maxima a block keeps in LDS: 8 bytes each, 32 KB, so that five blocks fit a CU.
-constexpr int32_t kTilesLds = 4096;
-constexpr int kPer = 8;  // templates per thread whose loads are issued together
+// Tiles whose running maxima a block keeps in LDS at most: 8 bytes each, 64 KB, so that two blocks fit a CU.
+constexpr int32_t kTilesLds = 8192;
 
 // A value other blocks may raise or lower meanwhile, read past the CU's own cache; used only to skip an atomic
 // that could not change it (both tables are monotone), never as the result.
@@ -50,15 +50,13 @@ __global__ void k_tile_fill(int32_t n_tiles, unsigned long long *mx, unsigned lo
     }
 }
 
-// LDS: the block's running maxima in LDS (n_tiles <= kTilesLds), else in mx itself.
-template <bool LDS>
+// The block's running maxima in LDS; kPer templates per thread whose loads are issued together.
+template <int kPer>
 __global__ __launch_bounds__(256) void k_tile_max(const double *__restrict__ stat, const int32_t *__restrict__ tile,
                                                   int64_t n, int32_t n_tiles, unsigned long long *mx) {
     extern __shared__ unsigned long long top[];
-    if constexpr (LDS) {
-        for (int t = threadIdx.x; t < n_tiles; t += 256) top[t] = peek(mx + t);
-        __syncthreads();
-    }
+    for (int t = threadIdx.x; t < n_tiles; t += 256) top[t] = peek(mx + t);
+    __syncthreads();
     const int64_t step = (int64_t)gridDim.x * 256 * kPer;
     for (int64_t base = (int64_t)blockIdx.x * 256 * kPer; base < n; base += step) {
         int32_t t[kPer];
@@ -70,22 +68,41 @@ __global__ __launch_bounds__(256) void k_tile_max(const double *__restrict__ sta
             ok[q] = i < n && tile_entry(stat, tile, i, n_tiles, t[q], b[q]);
         }
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            if (!ok[q]) continue;
-            if constexpr (LDS) {
-                if (b[q] > *(volatile unsigned long long *)(top + t[q])) atomicMax(top + t[q], b[q]);
-            } else {
-                if (b[q] > peek(mx + t[q])) atomicMax(mx + t[q], b[q]);
-            }
-        }
+        for (int q = 0; q < kPer; ++q)
+            if (ok[q] && b[q] > *(volatile unsigned long long *)(top + t[q])) atomicMax(top + t[q], b[q]);
     }
-    if constexpr (LDS) {
-        __syncthreads();
-        for (int t = threadIdx.x; t < n_tiles; t += 256)
-            if (top[t] > peek(mx + t)) atomicMax(mx + t, top[t]);
+    __syncthreads();
+    for (int t = threadIdx.x; t < n_tiles; t += 256)
+        if (top[t] > peek(mx + t)) atomicMax(mx + t, top[t]);
+}
+
+// One atomic per template, or per wave where all of its templates lie in one tile (a bank in the tiles' order).
+__global__ __launch_bounds__(256) void k_tile_max_each(const double *__restrict__ stat, const int32_t *__restrict__ tile,
+                                                       int64_t n, int32_t n_tiles, unsigned long long *mx) {
+    const int lane = threadIdx.x & 63;
+    const int64_t step = (int64_t)gridDim.x * 256;
+    for (int64_t base = (int64_t)blockIdx.x * 256; base < n; base += step) {
+        const int64_t i = base + threadIdx.x;
+        int32_t t = -1;
+        unsigned long long b = 0;
+        const bool ok = i < n && tile_entry(stat, tile, i, n_tiles, t, b);
+        const uint64_t act = __ballot(ok);
+        if (!act) continue;
+        const int first = __ffsll((unsigned long long)act) - 1, t0 = __shfl(t, first, 64);
+        if (__ballot(ok && t == t0) != act) {
+            if (ok) atomicMax(mx + t, b);
+            continue;
+        }
+        if (!ok) b = 0;
+        for (int o = 32; o > 0; o >>= 1) {
+            const unsigned long long other = __shfl_xor(b, o, 64);
+            b = other > b ? other : b;
+        }
+        if (lane == first) atomicMax(mx + t, b);
     }
 }
 
+template <int kPer>
 __global__ __launch_bounds__(256) void k_tile_arg(const double *__restrict__ stat, const int32_t *__restrict__ tile,
                                                   int64_t n, int32_t n_tiles,
                                                   const unsigned long long *__restrict__ mx, unsigned long long *arg) {
@@ -102,9 +119,19 @@ __global__ __launch_bounds__(256) void k_tile_arg(const double *__restrict__ sta
 #pragma unroll
         for (int q = 0; q < kPer; ++q) {
             const unsigned long long i = (unsigned long long)(base + q * 256 + threadIdx.x);
-            if (ok[q] && b[q] == mx[t[q]] && i < peek(arg + t[q])) atomicMin(arg + t[q], i);
+            if (ok[q] && b[q] == mx[t[q]] && (kPer == 1 || i < peek(arg + t[q]))) atomicMin(arg + t[q], i);
         }
     }
+}
+
+template <int kPer>
+void launch_tile_lds(const double *stat, const int32_t *tile, int64_t n, int32_t n_tiles, int64_t per,
+                     unsigned long long *mx, unsigned long long *arg, hipStream_t st) {
+    const int64_t want = (n + per - 1) / per, most = (n + 256 * kPer - 1) / (256 * kPer);
+    const unsigned nb = (unsigned)(want < 1024 ? want : 1024), na = (unsigned)(most < 2048 ? most : 2048);
+    hipLaunchKernelGGL(k_tile_max<kPer>, dim3(nb), dim3(256), sizeof(unsigned long long) * n_tiles, st, stat, tile, n,
+                       n_tiles, mx);
+    hipLaunchKernelGGL(k_tile_arg<kPer>, dim3(na), dim3(256), 0, st, stat, tile, n, n_tiles, mx, arg);
 }
 
 }  // namespace
@@ -116,20 +143,27 @@ hipError_t launch_tile_max(const double *stat, const int32_t *tile, int64_t n, i
     const unsigned tb = (unsigned)((n_tiles + 255) / 256);
     hipLaunchKernelGGL(k_tile_fill, dim3(tb), dim3(256), 0, st, n_tiles, mx, arg);
     if (n > 0) {
-        // Blocks: enough to fill the chip, each with at least one full batch and, where the maxima are kept in
-        // LDS, at least four templates per tile, so that loading and sending on the table stays the smaller part.
-        // The maximum pass takes at most 1024 blocks: each sends its maxima to the same few addresses (64 tiles, 4M
-        // templates: 53 us with 1953 blocks, 23 with 1024, 24 with 512, 37 with 256).
-        const bool lds = n_tiles <= kTilesLds;
-        const int64_t per = 256 * kPer > 4 * (int64_t)n_tiles || !lds ? 256 * kPer : 4 * (int64_t)n_tiles;
-        const int64_t want = (n + per - 1) / per, most = (n + 256 * kPer - 1) / (256 * kPer);
-        const unsigned nb = (unsigned)(want < 1024 ? want : 1024), na = (unsigned)(most < 2048 ? most : 2048);
-        if (lds)
-            hipLaunchKernelGGL(k_tile_max<true>, dim3(nb), dim3(256), sizeof(unsigned long long) * n_tiles, st, stat, tile,
-                               n, n_tiles, mx);
-        else
-            hipLaunchKernelGGL(k_tile_max<false>, dim3(nb), dim3(256), 0, st, stat, tile, n, n_tiles, mx);
-        hipLaunchKernelGGL(k_tile_arg, dim3(na), dim3(256), 0, st, stat, tile, n, n_tiles, mx, arg);
+        // Tables in LDS from 48 templates a tile on, and, as the chip wants some hundred blocks, each with a table to load
+        // and to send on, from n_tiles / 20 a tile on.  Both calls, tables against an atomic each, us, templates in any
+        // order: 1024 tiles: 20,000 15.4 / 15.4; 50,000 15.2 / 15.2; 100,000 14.4 / 18.0; 1M 26.5 / 129; 4096 tiles:
+        // 300,000 30 / 18; 1M 48 / 44; 4M 85 / 160; 8192 tiles: 1M 60 / 46; 4M 127 / 167.
+        const int64_t a_tile = n_tiles / 20 > 48 ? n_tiles / 20 : 48;
+        if (n_tiles <= kTilesLds && n >= a_tile * n_tiles) {
+            // From 131,072 templates on eight at a time, and four per tile and block, so that loading and sending on
+            // the tables stays the smaller part, else two and one, for more blocks (1024 tiles, 100,000 templates:
+            // 20.4 / 14.4 us; 1M: 26.5 / 41).  The maximum pass takes at most 1024 blocks: each sends its maxima to
+            // the same few addresses (64 tiles, 4M templates: 53 us with 1953 blocks, 23 with 1024, 24 with 512, 37
+            // with 256).
+            if (n >= 131072)
+                launch_tile_lds<8>(stat, tile, n, n_tiles, 4 * (int64_t)n_tiles > 2048 ? 4 * (int64_t)n_tiles : 2048, mx, arg, st);
+            else
+                launch_tile_lds<2>(stat, tile, n, n_tiles, n_tiles > 512 ? n_tiles : 512, mx, arg, st);
+        } else {
+            const int64_t want = (n + 255) / 256;
+            const unsigned nb = (unsigned)(want < 4096 ? want : 4096);
+            hipLaunchKernelGGL(k_tile_max_each, dim3(nb), dim3(256), 0, st, stat, tile, n, n_tiles, mx);
+            hipLaunchKernelGGL(k_tile_arg<1>, dim3(nb), dim3(256), 0, st, stat, tile, n, n_tiles, mx, arg);
+        }
     }
     return hipGetLastError();
 }

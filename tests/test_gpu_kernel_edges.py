@@ -36,6 +36,35 @@ def test_tile_max_at_block_and_table_edges(n, n_tiles, kind):
     assert np.array_equal(mx, rmx) and np.array_equal(arg, rarg)
 
 
+@pytest.mark.parametrize("n, n_tiles", [(63, 1), (3071, 64), (3072, 64), (52_223, 1024), (52_224, 1024), (131_071, 64),
+                                        (131_072, 64), (3_350_527, 8192), (3_350_528, 8192), (500_000, 8193)])
+@pytest.mark.parametrize("order", ["any", "tiles", "runs"])
+def test_tile_max_where_its_rule_changes(n, n_tiles, order):
+    """One template more or less than from which a block keeps its maxima in LDS, or takes more at a time, and the
+    largest table; templates in any order, in the tiles' order, and in runs of 64 with some of them left out (a wave
+    with a single tile sends one maximum)."""
+    tfsc = lib()
+    rng = np.random.default_rng(n + n_tiles)
+    note(f"tile max rule: {n} values, {n_tiles} tiles, {order}")
+    stat = np.round(rng.exponential(30.0, n), 2)
+    stat[rng.integers(0, n, n // 50)] = -1.0
+    tile = rng.integers(0, n_tiles, n).astype(np.int32)
+    if order == "tiles":
+        tile.sort()
+    if order == "runs":
+        tile = np.repeat(tile[: (n + 63) // 64], 64)[:n].copy()
+        tile[rng.integers(0, n, n // 3)] = -1
+    mx, arg = (t.cpu().numpy() for t in tfsc.tile_max(dev(stat), dev(tile), n_tiles))
+    ok = (tile >= 0) & (stat >= 0.0)
+    rmx = np.zeros(n_tiles)
+    np.maximum.at(rmx, tile[ok], stat[ok])
+    rarg = np.full(n_tiles, n, np.int64)
+    at = np.flatnonzero(ok & (stat == rmx[np.maximum(tile, 0)]))
+    np.minimum.at(rarg, tile[at], at)
+    rarg[rarg == n] = -1
+    assert np.array_equal(mx, rmx) and np.array_equal(arg, rarg)
+
+
 def _planes(store):
     """The store's pixels as complex128 [C][K][Nt]."""
     z = torch.view_as_complex(store.pix.to(torch.float64).contiguous())
