@@ -153,6 +153,15 @@ tfsc::SplitWs split_for(const tfsc_grid *g, int64_t n, size_t elem) {
 // Takes the split if the workspace has room for it.
 void use_split(const tfsc_grid *g, tfsc::StatLaunch &L, void *ws, size_t ws_bytes, bool log_mc) {
     const size_t elem = L.precision == 0 ? sizeof(double) : sizeof(float);
+    // Short rows in FP32 (one channel or 16 bits of two years, or less data): the L2s hold what neighbouring templates
+    // share without the units' help, and above three templates a wave (16-bit stores two; eight with a processing order)
+    // whole ones are as fast or faster.  Wide bank without an order, whole / split, us: two years of A+E, I16 (49 KB a
+    // row): 8000 1642 / 1684, 20,000 3422 / 3974, 80,000 12,143 / 15,596; one channel FP32 (49 KB): 8000 1259 / 1233,
+    // 20,000 2717 / 2913; 1232 tranches of M = 512, A+E, FP32 (20 KB): 12,000 666 / 660, 80,000 3360 / 3857; but A+E FP32
+    // of two years (98 KB): 20,000 3725 / 3244, 80,000 14,575 / 12,875.
+    const size_t cell = (size_t)L.C * (L.pix_dtype == 0 ? 16 : (L.pix_dtype == 1 ? 8 : 4)) + (L.rho ? 4 : 0);
+    const int64_t waves = (int64_t)device_cus() * 16;
+    if (L.precision == 1 && cell * (size_t)L.Nt < 65536 && L.n > waves * (L.order ? 8 : (is_16bit(L.pix_dtype) ? 2 : 3))) return;
     tfsc::SplitWs s = split_for(g, L.n, elem);
     const size_t base = stat_ws_bytes(g, L.n, log_mc);
     if (!s.units || ws_bytes < base + split_bytes(L.n, s, elem)) return;
