@@ -76,8 +76,10 @@ __device__ __forceinline__ void close_segments_ri(SegAccRi<NR> &acc, int upto, i
 // Bound: the memory behind L2 beside vector-ALU issue.  262,144 templates of the wide bank, two realisations, two-year grid
 // (with the two transforms): 63.3 ms from the work counter, 47.0 ms in runs of the processing order per XCD, whose L2s
 // then hold the rows that neighbouring templates share.
+// Two channels of four realisations need some 210 registers: at three waves per SIMD (168) the bin sums spilled (two years,
+// 20 templates 940 -> 880 us a call, 100,000 of the wide bank in runs 56.0 -> 43.3 ms with two).
 template <int C, int NR, class PixT>
-__global__ __launch_bounds__(256, 3) void k_stat_wave_ri(StatArgs a) {
+__global__ __launch_bounds__(256, C * NR > 4 ? 2 : 3) void k_stat_wave_ri(StatArgs a) {
 #pragma clang fp contract(fast)
     using R = float;
     constexpr int CC = NR * C;  // values per cell
