@@ -460,8 +460,11 @@ __device__ __forceinline__ void close_segments_multi(SegAccMulti &acc, int upto,
     }
 }
 
+// The LDS below lets two blocks of four waves on a CU, two waves per SIMD (three with one FP32 realisation a pass, one in
+// FP64), so the registers are those of two: at four, 35 to 174 of them spilled (two years, FP32, two realisations: 20
+// templates 1110 -> 900 us a call, 20,000 in processing order 8.4 -> 6.6 ms).
 template <int C, class R, class PixT, int LAYOUT, int RR>
-__global__ __launch_bounds__(256, 4) void k_stat_wave_multi(StatArgs a) {
+__global__ __launch_bounds__(256, 2) void k_stat_wave_multi(StatArgs a) {
     // LDS: u_pad[K + 20] (weights, as in k_stat_wave), then per wave the 21 weighted template
     // bins of each lane's tranche, cf[j][lane], and the tranche sums of its RR realisations,
     // zbuf[r][lane] = (Re z, Im z).
