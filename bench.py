@@ -181,7 +181,7 @@ def main():
                                   order=None if args.no_order else tfsc.processing_order(grid, tune))
         del tune, tune_seg
     kw = dict(block_waves=shape[0], groups_per_cu=shape[1])
-    log(f"launch shape: {shape[0]} waves per block, {shape[1]} blocks per CU; "
+    log(f"launch shape of the persistent grid: {shape[0]} waves per block, {shape[1]} blocks per CU; "
         f"order: {'bank order' if order is None else 'by f0 bin, then ln Mc class (device counting sort)'}")
 
     def step(store_dtype, layout, schedule, pix_out, res_out):
@@ -252,12 +252,14 @@ def main():
 
     # ---------------- the roofs: vector-ALU issue binds; HBM and algorithmic bytes reported beside it
     prof = measured_profile(n, args.chosen_store, args.chosen_layout, "bank" if order is None else "f0 bin, ln Mc")
+    launch = statistic_launch(n, args.chosen_store, order is not None, shape, g.n_channels * b_pix * g.n_tranches,
+                              torch.cuda.get_device_properties(dev).multi_processor_count, splits(tfsc, grid, n))
     k_s = k_ms / 1e3
     roofline = alu_roofline(prof, k_s)
     traffic = None if prof is None else prof.get("traffic_bytes")
     roofline.update({
         "traffic": traffic,
-        "kernel": "k_stat_wave" if order is None else "k_stat_runs",
+        "kernel": launch["kernel"],
         "kernel_ms": round(k_ms, 3),
         "profile_launch_shape": None if prof is None else prof.get("launch_shape"),
         "alg_bytes_per_launch": alg_bytes,
@@ -290,8 +292,8 @@ def main():
             "n_templates": n,
             "pixel_store": args.chosen_store,
             "pixel_layout": args.chosen_layout,
-            "schedule": "wave-per-template persistent",
-            "launch_shape": {"block_waves": kw["block_waves"], "groups_per_cu": kw["groups_per_cu"]},
+            "schedule": launch["schedule"],
+            "launch_shape": launch["launch_shape"],
             "order": "bank" if order is None else "f0 bin, ln Mc",
             "step": "transform + segment layout + processing order + bank statistic",
         },
@@ -948,6 +950,29 @@ CHOSEN_KERNELS = ("k_stat_runs<2, float, float, 2, false>", "k_stat_wave<2, floa
 SIMDS = 1024                  # 256 CUs x 4 SIMDs
 NOMINAL_CLOCK_HZ = 2.4e9
 CYCLES_PER_VALU = 4           # a wave64 instruction on a 16-lane SIMD
+
+
+def splits(tfsc, grid, n):
+    """Whether the library has scratch to share out the tranches of n templates (FP32 arithmetic)."""
+    import ctypes
+    g, opt = grid.c(), tfsc._options("f32")
+    size = [tfsc.lib().tfsc_workspace_bytes(ctypes.byref(g), n, ctypes.byref(opt), w)
+            for w in (tfsc._lib.WS_STATISTIC, tfsc._lib.WS_WHOLE)]
+    return size[0] > size[1]
+
+
+def statistic_launch(n, store, ordered, shape, row_bytes, cus, can_split):
+    """What the FP32 statistic of n templates launches: the kernel, how its waves take their work, and its launch shape
+    (the tuned one only of the persistent grid; the other kernels have four waves a block, one item each)."""
+    per_wave = 20 if row_bytes >= 65536 else (8 if ordered else (3 if store == "f32" else 2))
+    if can_split and n <= per_wave * 16 * cus:
+        return {"kernel": "k_stat_split", "schedule": "units of 64-tranche chunks, one per wave",
+                "launch_shape": {"block_waves": 4}}
+    if ordered and store == "f32" and n <= 1 << 25:
+        return {"kernel": "k_stat_runs", "schedule": "one wave per template, runs of the processing order per XCD",
+                "launch_shape": {"block_waves": 4}}
+    return {"kernel": "k_stat_wave", "schedule": "wave-per-template persistent",
+            "launch_shape": {"block_waves": shape[0], "groups_per_cu": shape[1]}}
 
 
 def stat_source_sha256():

@@ -176,15 +176,22 @@ typedef struct {
  *                        FP64.
  * schedule:  TFSC_SCHED_THREAD -- one thread per template walking its
  *                        tranches (the paper's mapping); any layout.
- *            TFSC_SCHED_WAVE   -- one 64-lane wavefront per template, lanes
- *                        over consecutive tranches, persistent grid pulling
- *                        templates from a device work counter; LAYER_MAJOR
- *                        or LAYER_MAJOR_CI.
- * block_waves / groups_per_cu: launch shape of the WAVE schedule, waves per
+ *            TFSC_SCHED_WAVE   -- 64-lane wavefronts, lanes over consecutive
+ *                        tranches; LAYER_MAJOR or LAYER_MAJOR_CI.  A
+ *                        persistent grid whose waves pull templates from a
+ *                        device work counter, or, where that is faster, one
+ *                        wave per template in runs of the processing order
+ *                        (F64 and F32 stores, up to 2^25 templates) or per
+ *                        unit of a template's tranches (small and medium
+ *                        banks; see tfsc_workspace_bytes).  The results of
+ *                        tfsc_bank_statistic are the same bits in all.
+ * block_waves / groups_per_cu: launch shape of the persistent grid, waves per
  * block (1..4) and resident blocks per compute unit (1..64); 0 = default
- * (4, 4); larger values return TFSC_ERR_ARG.  order: optional [n] permutation of template indices giving the
- * processing order (NULL = bank order); results are written at the
- * template's own index whatever the order.
+ * (4, 4); larger values return TFSC_ERR_ARG.  The other forms launch four
+ * waves per block whatever they say, and a tune_key.  order: optional [n]
+ * permutation of template indices giving the processing order (NULL = bank
+ * order); results are written at the template's own index whatever the
+ * order.
  * fresnel: TFSC_FRESNEL_PAPER -- the paper's Fresnel approximations (its
  *            rational forms for |z| <= 6, one-term asymptotic forms above;
  *            paper Sec. "Time-frequency waveform representation");
@@ -404,8 +411,9 @@ tfsc_status tfsc_bank_statistic_noalloc(const tfsc_grid *grid, const tfsc_pixels
  * TFSC_F32: spectra, response, pixel sums and their tangents in FP32, the
  * track, its tangents, the phases and every integer decision in FP64 (as in
  * the FP32 statistic); either arithmetic takes every pixel type and layout.
- * schedule and order are ignored, block_waves and groups_per_cu set the
- * launch.  Invalid and empty templates get 0.  Needs TFSC_WS_VJP workspace. */
+ * schedule and order are ignored; block_waves and groups_per_cu set the
+ * launch of whole templates (see tfsc_workspace_bytes).  Invalid and empty
+ * templates get 0.  Needs TFSC_WS_VJP workspace.                            */
 tfsc_status tfsc_statistic_vjp(const tfsc_grid *grid, const tfsc_pixels *pix, const tfsc_bank *bank,
                                const tfsc_segments *seg, const tfsc_options *opt, const double *seg_zn,
                                const double *g_stat, const double *g_seg, double *g_params, void *ws,
@@ -498,7 +506,8 @@ tfsc_status tfsc_link_lengths(const tfsc_grid *grid, const double *orbit, double
 
 /* Launch-shape autotuner of the WAVE statistic (paper Sec. "Hardware
  * acceleration and computational cost": large batches per launch): times
- * tfsc_bank_statistic on the given (tuning) bank for eight launch shapes
+ * the statistic of whole templates on the persistent grid, which is what a
+ * launch shape is for, on the given (tuning) bank for eight launch shapes
  * (waves per block x resident blocks per CU: 4x4, 4x3, 4x2, 2x8, 2x6, 2x4,
  * 1x12, 1x8), the fastest of two launches each, after one warm-up launch;
  * stores the fastest under tune_key for the rest of the process and writes

@@ -1,14 +1,14 @@
 """Batching around the statistic: launch-shape autotuning and HIP-graph replay over noise realisations.
 
 Paper Sec. "Hardware acceleration and computational cost": the method evaluates large batches of
-parameter sets per launch.  Here that is one persistent launch over the whole bank, with
+parameter sets per launch.  Here that is one launch over the whole bank, with
 
-* ``autotune``: the WAVE schedule's launch shape (waves per block, resident blocks per compute unit)
-  chosen by the library's tuner (tfsc_tune_statistic: candidates timed with HIP events on a tuning
+* ``autotune``: the launch shape of the WAVE schedule's persistent grid (waves per block, resident blocks per compute
+  unit; banks that are split or go in runs of a processing order have a fixed one) chosen by the library's tuner (tfsc_tune_statistic: candidates timed with HIP events on a tuning
   bank), cached in a JSON file keyed by the device and the workload's shape;
 * ``RealisationGraph``: the sequence transform(r) -> bank_statistic(r) for R noise realisations of
   the same grid, captured once into a HIP graph (torch.cuda.CUDAGraph) and replayed.  Every kernel
-  in it is a launch (work counters are cleared by a fill kernel, never by a memset node).
+  in it is a launch (work counters are cleared by a kernel, never by a memset node).
 
 Nothing here computes any part of the statistic: the work is done by libtfsc.so.
 """

@@ -92,3 +92,19 @@ def test_alu_roofline_against_the_rated_issue_rate():
     assert bench.alu_roofline(prof, 0.2)["frac"] == pytest.approx(0.5)
     none = bench.alu_roofline(None, 0.1)
     assert none["frac"] is None and none["peak"] == pytest.approx(614.4)
+
+
+def test_reported_launch_is_the_one_that_runs():
+    """The million-template bank in a processing order goes one wave per template, its 16-bit store and bank order on the
+    persistent grid with the tuned shape; a bank that can be split in units."""
+    long, short = 16 * 6144, 8 * 6144  # bytes of a row: A+E in FP32 and in 16 bits
+    assert bench.statistic_launch(1_000_020, "f32", True, (2, 8), long, 256, False)["kernel"] == "k_stat_runs"
+    assert bench.statistic_launch(1_000_020, "f32", True, (2, 8), long, 256, False)["launch_shape"] == {"block_waves": 4}
+    for store, ordered, row in (("f32", False, long), ("i16", True, short)):
+        r = bench.statistic_launch(1_000_020, store, ordered, (2, 8), row, 256, False)
+        assert r["kernel"] == "k_stat_wave" and r["launch_shape"] == {"block_waves": 2, "groups_per_cu": 8}
+    assert bench.statistic_launch((1 << 25) + 1, "f32", True, (4, 4), long, 256, False)["kernel"] == "k_stat_wave"
+    for n, store, ordered, row, kernel in ((20_000, "f32", False, long, "k_stat_split"), (20_000, "i16", False, short, "k_stat_wave"),
+                                           (20_000, "i16", True, short, "k_stat_split"), (12_288, "f32", False, short, "k_stat_split"),
+                                           (12_289, "f32", False, short, "k_stat_wave"), (40_000, "f32", True, short, "k_stat_runs")):
+        assert bench.statistic_launch(n, store, ordered, (4, 4), row, 256, True)["kernel"] == kernel, (n, store, ordered)
