@@ -500,14 +500,14 @@ static hipError_t run_fft_t(const TransformLaunch &L, double w2, uint32_t *layer
 
 // Which transforms a block runs one after the other, NIT of them, until its store.  Blocks of one transform (1, 1) fill the
 // chip where a set is short: it is done when its longest block is.  Above that the cells of two channels take both in one
-// block, for whole cells per store (M = 2048, FP32 store, 350 tranches: 15.0 us a call with one transform a block, 15.9
-// with a cell's two; 3,083: 57.6 against 46.0; M = 512, FP64 store, 500 tranches: 13.1 against 15.3).  One channel, and the
-// layouts that keep channels apart, stay with one transform (one channel, M = 2048, 3,083 tranches, FP32: 32 us against 43
-// with two pairs), as do FP32 cells of three channels (85 against 95).  From more than 1024 blocks on (768 run at once)
-// three channels' FP64 cells and 16-bit stores take a cell's channels, or two pairs of a channel: the writes of a cell join,
-// and a block sends half the maxima (M = 2048, C = 3, FP64: 500 tranches, 750 blocks, 24 us against 26; 3,083: 139 against
-// 117; 16 bits of one channel, 1,500: 38 against 39; 6,144: 97 against 89).  Not for M = 4096, whose blocks of 512 threads
-// come one or two to a CU (16 bits of one channel, 3,083 tranches: 90 against 112).
+// block, for whole cells per store (M = 512, FP64 store, 500 tranches: 13.2 us a call with one transform a block, 15.0
+// with a cell's two; M = 2048, FP32, 3,083: 54.8 against 45.4).  One channel, and the layouts that keep channels apart,
+// stay with one transform (one channel, M = 2048, 3,083 tranches, FP32: 32 us against 43 with two pairs), as do FP32 cells
+// of three channels (M = 1024, 500: 15 against 20; M = 2048, 3,083: 80 against 77).  From more than 1024 blocks on (768
+// run at once) three channels' FP64 cells and 16-bit stores take a cell's channels, or two pairs of a channel: the writes
+// of a cell join, and a block sends half the maxima (M = 2048, C = 3, FP64: 500 tranches, 750 blocks, 24 us against 26;
+// 3,083: 137 against 124; 16 bits of one channel, 1,500: 37 against 38; 6,144: 96 against 87).  Not for M = 4096, whose
+// blocks of 512 threads come one or two to a CU (16 bits of one channel, 3,083 tranches: 85 against 97).
 // The 16-byte stores of FP32 A+E cells need a store aligned to them; another one takes the one-channel form, which writes
 // any layout 8 or 16 bytes at a time.
 template <class R, class XT, class OutT>
